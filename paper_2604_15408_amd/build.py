@@ -15,7 +15,7 @@ ROOT = PKG.parent
 CSRC = PKG / "csrc"
 LIB = PKG / "libragged_hip.so"
 BUILD_DIR = PKG / "_build"
-SOURCES = ["ragged_api.hip", "pack_unpack.hip", "attn.hip", "linear.hip", "mask.hip"]
+SOURCES = ["ragged_api.hip", "pack_unpack.hip", "attn.hip", "linear.hip", "linear_f16.hip", "linear_bf16.hip", "mask.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -33,7 +33,7 @@ HIPCC_FLAGS = [
 # by first use).  Measured side by side: attention and the 36-kernel pipeline 2-3 % faster; the linear
 # layers, whose launches last 8-90 us, 1-2 % slower with it, so they are built without.
 PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=14"]
-PER_FILE_FLAGS = {"linear.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "attn.hip": PRELOAD, "pack_unpack.hip": PRELOAD,
+PER_FILE_FLAGS = {"attn.hip": PRELOAD, "pack_unpack.hip": PRELOAD,
                   "mask.hip": PRELOAD}
 
 

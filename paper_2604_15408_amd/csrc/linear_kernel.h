@@ -1,0 +1,456 @@
+// linear_kernel: y[m][n] = act( sum_k x[m][k] * w[n][k] + bias[n] ) (+ residual[m][n]) over packed rows, on MFMA
+// (internal; the rule that picks a tile shape is in linear.hip, one source per input type instantiates the kernel).
+//
+// x [rows, K], w [N, K]: both operands are contiguous along k, which is how an MFMA lane wants them (8 consecutive k per
+// 16-byte read).  The product is formed transposed (features x tokens: w is the A operand), and MFMA row m' of feature
+// tile j stands for feature 32*(j/2) + 8*(m'/4) + 4*(j%2) + m'%4, so that a lane ends up with 8 consecutive features of a
+// token and the four lanes of a token store 64 contiguous bytes.
+//
+// One work-group of four wavefronts per CU, one wavefront per SIMD, each owning 16 NJ features x 16 MT tokens: with the
+// whole register file to itself a wavefront holds up to 128 x 128 accumulators, and LDS traffic per product is half of
+// that of eight wavefronts of 64 x 128, which kept the LDS pipe busy as long as the matrix core (25 216 rows, us before
+// and now: 2304 x 768 98 and 86, 768 x 3072 141 and 101; an 8192^3 product ran at 1.17 PFLOP/s and runs at 1.41).  Large
+// problems are bound by the clock the chip holds under that load (1.3 to 1.6 GHz at the K = 768 layers, with 90 % of the
+// cycles issuing matrix work), small ones by the time of a step (LDS round trip, barrier) and by launch and first loads.
+//
+// With a single wavefront nothing else fills the gap an instruction leaves, so the loop is laid out by issue slots.
+// Measured: one instruction between two MFMAs is free, a second independent VALU too, anything more (or an address
+// computed in front of an LDS read) adds 4 cycles to the 16 of an MFMA, a load about 6.  So fragment reads have their
+// addresses ready (immediate offsets; the six registers move from stage to stage in slots of their own), a load's M0 set-up and the
+// load sit on the two sides of a product, and everything is spread evenly: a 256 x 256 step of 128 MFMAs takes 2300
+// cycles (2755 with reads and loads issued as they come).  The products are inline assembly: accumulators stay in the
+// accumulation registers without copies, and the order is kept.
+//
+// Operand tiles (rows x 64 k = 128-byte rows) are brought into LDS by direct loads, row-major with the chunk swizzle
+// c ^ ((row>>1)&3) that makes every 16-byte fragment read conflict-free, in a ring of as many stages as fit 160 KB.
+// A step is two halves of 32 k; fragments of the next half are read while the products of this one run:
+//   * more than two stages: one barrier per step, between the halves.  The ring is refilled half a step at a time (w with
+//     the first half, x with the second);
+//   * two stages (tiles of 192 rows and more): x of both halves is held a step ahead, which frees the x part of a stage at
+//     the start of its step and the w part in the middle, so that its loads spread over the whole step as well (issued
+//     in one half they queue up: 4 x 16 KB at 64 bytes a cycle).
+// The tiles of a work-group follow each other without a break: the last steps of one load the first of the next.
+//
+// Epilogue in registers: bias, GELU, residual, one rounding, 16-byte stores.
+#pragma once
+
+#include <type_traits>
+
+#include "common.h"
+#include "linear_epilogue.h"
+#include "mfma_lds.h"
+
+namespace ragged {
+
+constexpr int kTK = 64;                          // contraction elements per step: 128-byte LDS rows
+constexpr int kLinWaves = 4;                     // one wavefront per SIMD
+constexpr int kLdsBytes = 160 * 1024;
+
+struct LinearArgs {
+    const uint16_t* x;
+    const uint16_t* w;
+    const uint16_t* bias;
+    const uint16_t* res;                         // may alias y
+    uint16_t* y;
+    const int32_t* rows_dev;
+    int rows_cap, N, K, act;
+    int n_tiles;                                 // N / (32 NJ)
+    int panel;                                   // feature tiles of a panel, see tile_of()
+    uint32_t panel_magic, last_magic;            // div_magic() of panel and of the last panel's width
+};
+
+#define ALWAYS_INLINE __attribute__((always_inline))
+
+// acc += A B (FIRST: acc = A B), the accumulator in the accumulation registers.
+#define MFMA_TEXT(dt) "v_mfma_f32_16x16x32_" dt " %0, %1, %2, "
+template <bool FIRST>
+__device__ __forceinline__ void mma_acc(F16, const u32x4& a, const u32x4& b, f32x4& acc) {
+    if (FIRST) asm volatile(MFMA_TEXT("f16") "0" : "=a"(acc) : "v"(a), "v"(b));
+    else asm volatile(MFMA_TEXT("f16") "%0" : "+a"(acc) : "v"(a), "v"(b));
+}
+template <bool FIRST>
+__device__ __forceinline__ void mma_acc(BF16, const u32x4& a, const u32x4& b, f32x4& acc) {
+    if (FIRST) asm volatile(MFMA_TEXT("bf16") "0" : "=a"(acc) : "v"(a), "v"(b));
+    else asm volatile(MFMA_TEXT("bf16") "%0" : "+a"(acc) : "v"(a), "v"(b));
+}
+// The same with one global->LDS load: lane i fetches the 16 bytes at rsrc.base + voff + soff (zeros past
+// rsrc.num_records) and the hardware stores them at LDS address dst + off + 16*i.  Its two instructions sit in front of
+// and behind the product, one issue slot each.
+#define DMA_HEAD "s_add_u32 m0, %3, %4\n\t"
+#define DMA_TAIL "\n\tbuffer_load_dwordx4 %5, %6, %7 offen lds"
+#define DMA_ARGS "s"(dst), "i"(off), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0", "scc"
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+template <bool FIRST>
+__device__ __forceinline__ void mma_acc_dma(F16, const u32x4& a, const u32x4& b, f32x4& acc, uint32_t dst, uint32_t off,
+                                            uint32_t voff, const u32x4& rsrc, uint32_t soff) {
+    if (FIRST) asm volatile(DMA_HEAD MFMA_TEXT("f16") "0" DMA_TAIL : "=&a"(acc) : "v"(a), "v"(b), DMA_ARGS);
+    else asm volatile(DMA_HEAD MFMA_TEXT("f16") "%0" DMA_TAIL : "+a"(acc) : "v"(a), "v"(b), DMA_ARGS);
+}
+template <bool FIRST>
+__device__ __forceinline__ void mma_acc_dma(BF16, const u32x4& a, const u32x4& b, f32x4& acc, uint32_t dst, uint32_t off,
+                                            uint32_t voff, const u32x4& rsrc, uint32_t soff) {
+    if (FIRST) asm volatile(DMA_HEAD MFMA_TEXT("bf16") "0" DMA_TAIL : "=&a"(acc) : "v"(a), "v"(b), DMA_ARGS);
+    else asm volatile(DMA_HEAD MFMA_TEXT("bf16") "%0" DMA_TAIL : "+a"(acc) : "v"(a), "v"(b), DMA_ARGS);
+}
+__device__ __forceinline__ void buf_dma16(uint32_t dst, uint32_t voff, const u32x4& rsrc, uint32_t soff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(dst), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
+__device__ __forceinline__ float read_acc(float a) {
+    float v;
+    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(a));
+    return v;
+}
+__device__ __forceinline__ u32x4 lds_vec(uint32_t addr) {
+    return *reinterpret_cast<const lds_u32x4*>(static_cast<uintptr_t>(addr));
+}
+
+// The m-th product's position in rows of n: rows are walked to and fro, so that one operand of two stays from each
+// product to the next (the matrix core then draws less power, which is what limits the clock in these kernels).
+constexpr int snake(int m, int n) { return (m / n) % 2 ? n - 1 - m % n : m % n; }
+// Which of `count` things spread evenly over `slots` issue slots goes with slot s (-1: none).
+constexpr int spread_at(int s, int slots, int count) {
+    for (int d = 0; d < count; ++d)
+        if ((2 * d + 1) * slots / (2 * count) == s) return d;
+    return -1;
+}
+
+// Number of LDS stages: as many as fit, up to eight.
+constexpr int linear_stages(int NJ, int MT) {
+    const int fit = kLdsBytes / (32 * (NJ + MT) * kTK * 2);
+    return fit < 8 ? fit : 8;
+}
+
+template <typename In, int NJ, int MT>
+__global__ __launch_bounds__(kWaveSize * kLinWaves, 1)
+void linear_kernel(LinearArgs p) {
+    constexpr int TN = 32 * NJ, TM = 32 * MT;                  // features x tokens of a tile, 2 x 2 wavefronts
+    constexpr int kXBytes = TM * kTK * 2, kWBytes = TN * kTK * 2;
+    constexpr int kStageBytes = kXBytes + kWBytes;
+    constexpr int STAGES = linear_stages(NJ, MT);
+    static_assert(STAGES >= 2, "two stages must fit");
+    constexpr bool TWO = STAGES == 2;
+    constexpr bool RELAX = STAGES >= 4;
+    constexpr int kAheadX = TWO ? 2 : (RELAX ? STAGES - 1 : STAGES);   // step whose x loads go with half B (TWO: A) of step 0
+    constexpr int kAheadW = TWO ? 2 : kAheadX - 1;                     // ... w loads with half A (TWO: B)
+    __shared__ __attribute__((aligned(1024))) uint4 stage_lds[STAGES * kStageBytes / 16];
+
+    const int N = p.N;
+    int rows = p.rows_cap;
+    if (p.rows_dev) { const int r = *p.rows_dev; rows = r < rows ? r : rows; }
+    rows = __builtin_amdgcn_readfirstlane(rows);
+    const int m_tiles = (rows + TM - 1) / TM;
+    const int total = m_tiles * p.n_tiles;
+    const int xcd = blockIdx.x % kXcds;
+    const int per_xcd = (total + kXcds - 1) / kXcds;
+    const int t_end = per_xcd * (xcd + 1) < total ? per_xcd * (xcd + 1) : total;
+    const int stride = gridDim.x / kXcds;
+    const int t_first = per_xcd * xcd + blockIdx.x / kXcds;
+    if (t_first >= t_end) return;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWaveSize - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15;
+    const int g = lane >> 4;
+    const int wn = wave & 1, wm = wave >> 1;
+
+    // tile number -> first row, first feature.  Panels of `panel` feature tiles, one after the other; inside a panel the
+    // feature tiles of a token tile come together.
+    auto tile_of = [&](int t, int& m0, int& n0) ALWAYS_INLINE {
+        int first = 0, width = p.panel;
+        while (t >= m_tiles * width) {                         // a few panels at most
+            t -= m_tiles * width;
+            first += width;
+            width = p.n_tiles - first < p.panel ? p.n_tiles - first : p.panel;
+        }
+        uint32_t mq, nr;
+        divmod((uint32_t)t, (uint32_t)width, width == p.panel ? p.panel_magic : p.last_magic, mq, nr);
+        m0 = (int)mq * TM;
+        n0 = (first + (int)nr) * TN;
+    };
+
+    // ---- loads.  Instruction d of this wavefront covers rows 8*(count*wave + d) + lane/8 of its operand tile; the
+    // lane's LDS slot is position lane%8 of that row = chunk (lane%8) ^ ((row>>1)&3).
+    constexpr int kXI = MT, kWI = NJ;                          // load instructions per wavefront and step
+    const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)stage_lds);
+    const uint32_t row_bytes = (uint32_t)p.K * 2u;
+    const uint32_t chunk = 16u * ((lane & 7) ^ ((lane >> 4) & 3));
+    const int ksteps = p.K / kTK;
+    uint32_t voff_x[kXI], voff_w[kWI];
+#pragma unroll
+    for (int i = 0; i < kXI; ++i) voff_x[i] = (uint32_t)(8 * (kXI * wave + i) + (lane >> 3)) * row_bytes + chunk;
+#pragma unroll
+    for (int i = 0; i < kWI; ++i) voff_w[i] = (uint32_t)(8 * (kWI * wave + i) + (lane >> 3)) * row_bytes + chunk;
+    const uint32_t x_dst = kXI * 1024 * wave, w_dst = kXBytes + kWI * 1024 * wave;
+
+    // Two cursors walk (tile, step) ahead of the arithmetic.  Past the last tile the range is empty: such loads touch no
+    // memory.  Rows past the end of x are out of range too and arrive as zeros (their results are not stored).
+    u32x4 x_rsrc, w_rsrc;
+    uint32_t x_soff = 0, w_soff = 0;
+    int x_tile = t_first, w_tile = t_first;
+    auto set_rsrc = [&](u32x4& r, const uint16_t* base, uint32_t bytes) ALWAYS_INLINE {
+        const uint64_t a = reinterpret_cast<uint64_t>(base);
+        r[0] = __builtin_amdgcn_readfirstlane((uint32_t)a);
+        r[1] = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+        r[2] = __builtin_amdgcn_readfirstlane(bytes);
+        r[3] = 0x00020000u;
+    };
+    auto set_x = [&]() ALWAYS_INLINE {
+        int m0, n0;
+        tile_of(x_tile < t_end ? x_tile : t_first, m0, n0);
+        const int live = rows - m0 < TM ? rows - m0 : TM;
+        set_rsrc(x_rsrc, p.x + (int64_t)m0 * p.K, x_tile < t_end ? (uint32_t)live * row_bytes : 0u);
+        x_soff = 0;
+    };
+    auto set_w = [&]() ALWAYS_INLINE {
+        int m0, n0;
+        tile_of(w_tile < t_end ? w_tile : t_first, m0, n0);
+        set_rsrc(w_rsrc, p.w + (int64_t)n0 * p.K, w_tile < t_end ? (uint32_t)TN * row_bytes : 0u);
+        w_soff = 0;
+    };
+    auto next_x = [&]() ALWAYS_INLINE {
+        x_soff += kTK * 2;
+        if (x_soff == row_bytes) { x_tile += stride; set_x(); }
+    };
+    auto next_w = [&]() ALWAYS_INLINE {
+        w_soff += kTK * 2;
+        if (w_soff == row_bytes) { w_tile += stride; set_w(); }
+    };
+
+    // ---- LDS addresses of this lane's operands: x (B operand) row 16 mt + col, w (A operand) of feature tile j: row
+    // 32 (j/2) + 8 (col/4) + 4 (j%2) + col%4; chunk 2g + half
+    const int x_row = wm * 16 * MT + col;
+    uint32_t rb[2], ra[2][2];                                  // [half], [half][j % 2]
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        rb[h] = lds0 + x_row * 128 + 16 * ((2 * g + h) ^ ((x_row >> 1) & 3));
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int w_row = wn * 16 * NJ + 8 * (col >> 2) + 4 * j + (col & 3);
+            ra[h][j] = lds0 + kXBytes + w_row * 128 + 16 * ((2 * g + h) ^ ((w_row >> 1) & 3));
+        }
+    }
+    f32x4 acc[NJ][MT];
+    u32x4 a0[NJ], b0[MT], a1[NJ], b1[MT];
+    auto read_a = [&](int h, int j) ALWAYS_INLINE { return lds_vec(ra[h][j & 1] + (j >> 1) * 4096); };
+    auto read_b = [&](int h, int mt) ALWAYS_INLINE { return lds_vec(rb[h] + mt * 2048); };
+
+    constexpr int NS = NJ * MT;                                // products of half a step = issue slots
+    // ---- first half of a step: products of (a0, b0)
+    auto half_a = [&](auto first_tag, uint32_t fill, uint32_t delta) ALWAYS_INLINE {
+        constexpr bool FIRST = decltype(first_tag)::value;
+        constexpr int kSync = TWO ? NS / 8 : 0, kLeft = NS - kSync;
+#pragma unroll
+        for (int m = 0; m < kSync; ++m) {
+            if (m == 1) rb[1] += delta;
+            __builtin_amdgcn_sched_barrier(0);
+            mma_acc<FIRST>(In{}, a0[m / MT], b0[snake(m, MT)], acc[m / MT][snake(m, MT)]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (TWO) {
+            __builtin_amdgcn_s_waitcnt(0xC07F);                // lgkmcnt(0)
+            __syncthreads();
+        }
+        constexpr int kLoads = TWO ? kXI : kWI;
+        constexpr int kReads = TWO ? NJ : NJ + MT;
+#pragma unroll
+        for (int m = kSync; m < NS; ++m) {
+            const int q = m - kSync;
+#pragma unroll
+            for (int r = 0; r < kReads; ++r)
+                if (r * kLeft * 3 / (4 * kReads) == q) {
+                    if (r < NJ) a1[r < NJ ? r : 0] = read_a(1, r);
+                    else b1[r - NJ < MT && r >= NJ ? r - NJ : 0] = read_b(1, r - NJ);
+                }
+            if (q == kLeft - 1) ra[0][0] += delta;
+            if (q == (kLeft >= 4 ? kLeft - 3 : kLeft - 1)) ra[0][1] += delta;
+            if (q == (kLeft >= 8 ? kLeft - 5 : kLeft - 1)) rb[0] += delta;
+            const int d = spread_at(q, kLeft, kLoads);
+            __builtin_amdgcn_sched_barrier(0);
+            if (d < 0) mma_acc<FIRST>(In{}, a0[m / MT], b0[snake(m, MT)], acc[m / MT][snake(m, MT)]);
+            else if (TWO) mma_acc_dma<FIRST>(In{}, a0[m / MT], b0[snake(m, MT)], acc[m / MT][snake(m, MT)], fill + x_dst, d * 1024, voff_x[d < kXI ? d : 0], x_rsrc, x_soff);
+            else mma_acc_dma<FIRST>(In{}, a0[m / MT], b0[snake(m, MT)], acc[m / MT][snake(m, MT)], fill + w_dst, d * 1024, voff_w[d < kWI ? d : 0], w_rsrc, w_soff);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (TWO) next_x();
+        else next_w();
+    };
+    // ---- second half: products of (a1, b1); fragments of the next step
+    auto half_b = [&](uint32_t fill, uint32_t delta) ALWAYS_INLINE {
+        constexpr int kReads = NJ + MT;
+#pragma unroll
+        for (int m = 0; m < NS; ++m) {
+#pragma unroll
+            for (int r = 0; r < kReads; ++r)
+                if ((TWO ? 2 * r : r * NS * 3 / (4 * kReads)) == m) {
+                    if (r < NJ) a0[r < NJ ? r : 0] = read_a(0, r);
+                    else b0[r - NJ < MT && r >= NJ ? r - NJ : 0] = read_b(0, r - NJ);
+                }
+            if (TWO && m % NJ == 1 && m > NJ) b1[m / NJ - 1] = read_b(1, m / NJ - 1);
+            if (m == NS - 1) ra[1][0] += delta;
+            if (m == (NS >= 4 ? NS - 3 : NS - 1)) ra[1][1] += delta;
+            if (!TWO && m == (NS >= 8 ? NS - 5 : NS - 1)) rb[1] += delta;
+            const int d = spread_at(m, NS, TWO ? kWI : kXI);
+            __builtin_amdgcn_sched_barrier(0);
+            if (d < 0) mma_acc<false>(In{}, a1[snake(m, NJ)], b1[m / NJ], acc[snake(m, NJ)][m / NJ]);
+            else if (TWO) mma_acc_dma<false>(In{}, a1[snake(m, NJ)], b1[m / NJ], acc[snake(m, NJ)][m / NJ], fill + w_dst, d * 1024, voff_w[d < kWI ? d : 0], w_rsrc, w_soff);
+            else mma_acc_dma<false>(In{}, a1[snake(m, NJ)], b1[m / NJ], acc[snake(m, NJ)][m / NJ], fill + x_dst, d * 1024, voff_x[d < kXI ? d : 0], x_rsrc, x_soff);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (TWO) {
+            b1[MT - 1] = read_b(1, MT - 1);
+            __builtin_amdgcn_sched_barrier(0);
+            next_w();
+        } else {
+            next_x();
+        }
+    };
+
+    int m0, n0;                                                // the tile being computed
+    uint4 bias_raw[NJ / 2];
+    auto load_bias = [&]() ALWAYS_INLINE {
+#pragma unroll
+        for (int jp = 0; jp < NJ / 2; ++jp)
+            bias_raw[jp] = p.bias ? *reinterpret_cast<const uint4*>(p.bias + n0 + wn * 16 * NJ + 32 * jp + 8 * g) : make_uint4(0, 0, 0, 0);
+    };
+    set_x();
+    set_w();
+    {
+        constexpr int kFillX = TWO ? 2 : kAheadX, kFillW = TWO ? 2 : kAheadW;
+#pragma unroll
+        for (int st = 0; st < kFillX; ++st) {
+#pragma unroll
+            for (int d = 0; d < kXI; ++d) buf_dma16(lds0 + st * kStageBytes + x_dst + d * 1024, voff_x[d], x_rsrc, x_soff);
+            next_x();
+            if (st < kFillW) {
+#pragma unroll
+                for (int d = 0; d < kWI; ++d) buf_dma16(lds0 + st * kStageBytes + w_dst + d * 1024, voff_w[d], w_rsrc, w_soff);
+                next_w();
+            }
+        }
+        wait_vm<(kFillX - 1) * kXI + (kFillW - 1) * kWI>();    // step 0 has landed
+    }
+    tile_of(t_first, m0, n0);
+    load_bias();
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) a0[j] = read_a(0, j);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) b0[mt] = read_b(0, mt);
+    if (TWO)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) b1[mt] = read_b(1, mt);
+
+    // stage numbers: s of the current step, s_next of the next, fill_a / fill_b the ones that half A / B load into
+    auto wrap = [&](uint32_t s) ALWAYS_INLINE { return s == lds0 + (STAGES - 1) * kStageBytes ? lds0 : s + kStageBytes; };
+    uint32_t s = lds0;
+    uint32_t fill_a = TWO ? lds0 : lds0 + kAheadW * kStageBytes;
+    uint32_t fill_b = TWO ? lds0 : lds0 + (kAheadX % STAGES) * kStageBytes;
+    bool landed = false;
+    auto step = [&](auto first_tag) ALWAYS_INLINE {
+        const uint32_t s_next = wrap(s);
+        const uint32_t delta = s_next - s;
+        if (TWO) __builtin_amdgcn_s_waitcnt(0xC17F);           // lgkmcnt(1): all but the last fragment
+        half_a(first_tag, fill_a, delta);
+        if (!decltype(first_tag)::value || !landed)            // the next step has landed
+            wait_vm<TWO ? kXI : (kAheadX - 2) * (kXI + kWI)>();
+        if (RELAX) {
+            asm volatile("s_barrier" ::: "memory");
+        } else {
+            __builtin_amdgcn_s_waitcnt(0xC07F);
+            __syncthreads();
+        }
+        half_b(fill_b, delta);
+        s = s_next;
+        fill_a = wrap(fill_a);
+        fill_b = wrap(fill_b);
+    };
+
+    for (int t = t_first; t < t_end; t += stride) {
+        step(std::true_type{});
+        for (int kt = 1; kt < ksteps; ++kt) step(std::false_type{});
+        // the last products have to leave the matrix core before other instructions may read them
+        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+
+        // ---- epilogue: this lane owns, for row m0 + wm*16*MT + 16 mt + col, features n_base + 32 jp + 0..7
+        const int n_base = n0 + wn * 16 * NJ + 8 * g;
+        const int m_base = m0 + wm * 16 * MT + col;
+        float bias8[NJ / 2][8];
+#pragma unroll
+        for (int jp = 0; jp < NJ / 2; ++jp) unpack8(In{}, bias_raw[jp], bias8[jp]);
+        if (t + stride < t_end) {
+            tile_of(t + stride, m0, n0);
+            load_bias();                                       // the next tile's
+        }
+        auto offset = [&](int mt) ALWAYS_INLINE -> int64_t {
+            const int m = m_base + 16 * mt;
+            return (int64_t)(m < rows ? m : rows - 1) * N + n_base;
+        };
+        auto finish = [&](auto act_tag, auto res_tag) ALWAYS_INLINE {
+            constexpr bool ACT = decltype(act_tag)::value, RES = decltype(res_tag)::value;
+            constexpr int kMost = NJ == 8 ? (MT == 8 ? 2 : 3) : 4;
+            constexpr int kAhead = kMost < MT ? kMost : MT;    // residual rows in flight
+            uint4 r_raw[kAhead][NJ / 2];
+            auto load_res = [&](int mt) ALWAYS_INLINE {
+                const int64_t off = offset(mt);
+#pragma unroll
+                for (int jp = 0; jp < NJ / 2; ++jp) r_raw[mt % kAhead][jp] = *reinterpret_cast<const uint4*>(p.res + off + 32 * jp);
+            };
+            if (RES)
+#pragma unroll
+                for (int mt = 0; mt < kAhead; ++mt) load_res(mt);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                uint4 out[NJ / 2];
+#pragma unroll
+                for (int jp = 0; jp < NJ / 2; ++jp) {
+                    float v[8], r8[8];
+                    if (RES) unpack8(In{}, r_raw[mt % kAhead][jp], r8);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        float f = read_acc(acc[2 * jp + e / 4][mt][e % 4]) + bias8[jp][e];
+                        if (ACT) f = gelu_erf(f);
+                        if (RES) f += r8[e];
+                        v[e] = f;
+                    }
+                    out[jp] = pack8(In{}, v);
+                }
+                if (mt == 0) wait_vm<RES ? (kAhead - 1) * (NJ / 2) : 0>();   // what the next tile starts with has landed
+                const int64_t off = offset(mt);
+                if (m_base + 16 * mt < rows)
+#pragma unroll
+                    for (int jp = 0; jp < NJ / 2; ++jp) *reinterpret_cast<uint4*>(p.y + off + 32 * jp) = out[jp];
+                if (RES && mt + kAhead < MT) load_res(mt + kAhead);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        if (p.act) {
+            if (p.res) finish(std::true_type{}, std::true_type{});
+            else finish(std::true_type{}, std::false_type{});
+        } else {
+            if (p.res) finish(std::false_type{}, std::true_type{});
+            else finish(std::false_type{}, std::false_type{});
+        }
+        landed = true;
+    }
+}
+
+// The tile shapes there are, as {NJ, MT}: 32 NJ features x 32 MT tokens.
+#define LINEAR_SHAPES(X) X(8, 8) X(8, 7) X(8, 6) X(8, 5) X(8, 4) X(6, 4) X(6, 3) X(6, 2) X(4, 4) X(4, 3) X(4, 2) X(2, 4) X(2, 2)
+
+template <typename In>
+hipError_t launch_linear_tile(int nj, int mt, int groups, const LinearArgs& args, hipStream_t stream) {
+#define LINEAR_CASE(NJ, MT) \
+    if (nj == NJ && mt == MT) return launch_kernel(linear_kernel<In, NJ, MT>, dim3(groups), dim3(kWaveSize * kLinWaves), stream, args);
+    LINEAR_SHAPES(LINEAR_CASE)
+#undef LINEAR_CASE
+    return hipErrorInvalidValue;
+}
+hipError_t launch_linear_f16(int nj, int mt, int groups, const LinearArgs& args, hipStream_t stream);
+hipError_t launch_linear_bf16(int nj, int mt, int groups, const LinearArgs& args, hipStream_t stream);
+
+}  // namespace ragged

@@ -88,6 +88,22 @@ def test_linear_every_launch_shape(dtype, act, residual):
     check_linear(700, 1024, 192, rows=650, cap=800, seed=8, hint=650, **kw)       # odd number of k-steps: no split
 
 
+@pytest.mark.parametrize("hint,N,K", [
+    (3600, 4096, 64), (3100, 4096, 128), (3400, 3072, 128), (2100, 4096, 256), (2700, 2304, 128),   # 256 features x 256 .. 128 rows
+    (3100, 1536, 192), (5500, 576, 64), (1800, 1152, 64),                                           # 192 features x 128, 96, 64 rows
+    (2700, 1152, 128), (4100, 512, 64), (900, 1152, 64),                                            # 128 features x 128, 96, 64 rows
+    (1800, 576, 64), (100, 64, 64)])                                                                # 64 features x 128, 64 rows
+def test_linear_every_tile_shape(hint, N, K):
+    """Each tile shape (picked through the row estimate) at row counts that end just before, on and just behind a tile
+    edge; one k-step, fewer and more k-steps than the LDS ring has stages; several tiles per work-group."""
+    for i, rows in enumerate((1, 127, 193, 258)):
+        check_linear(rows, N, K, dtype=("f16", "bf16")[i % 2], act=("none", "gelu")[i // 2], residual=i % 2 == 0,
+                     rows=rows, cap=hint, seed=50 + i, hint=hint)
+    if N <= 1536:
+        check_linear(hint, N, 64, seed=60, residual=True)
+        check_linear(130, N, 768, rows=129, cap=hint, seed=61, hint=hint)
+
+
 @pytest.mark.parametrize("M", [12608, 6304])
 @pytest.mark.parametrize("N,K,act,residual", [(2304, 768, "none", False), (768, 768, "none", True),
                                                (3072, 768, "gelu", False), (768, 3072, "none", True)])
