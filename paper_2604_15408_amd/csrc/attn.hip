@@ -93,13 +93,25 @@ template <bool START>
 __device__ __forceinline__ void pv_block(BF16, const uint4 (&vt)[4], const float (&p)[8], f32x4 (&o)[4],
                                          f32x4& l) {
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    bf16x8 hi, lo, ones;
+    // Two probabilities at a time: one packed conversion, the rounded values back as bits of its result (a shift and a
+    // mask), two subtractions, one packed conversion.  Written element by element the compiler converts every P_hi twice
+    // (117 instead of 101 VALU instructions per 16-query x 64-key tile).
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    uint32_t hi_w[4], lo_w[4];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        hi[e] = (__bf16)p[e];
-        lo[e] = (__bf16)(p[e] - (float)hi[e]);
-        ones[e] = (__bf16)1.0f;
+    for (int e = 0; e < 4; ++e) {
+        const f32x2 pair = {p[2 * e], p[2 * e + 1]};
+        hi_w[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2));
+        const f32x2 rest = {p[2 * e] - __builtin_bit_cast(float, hi_w[e] << 16),
+                            p[2 * e + 1] - __builtin_bit_cast(float, hi_w[e] & 0xffff0000u)};
+        lo_w[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, bf16x2));
     }
+    const bf16x8 hi = as_vec8<bf16x8>(make_uint4(hi_w[0], hi_w[1], hi_w[2], hi_w[3]));
+    const bf16x8 lo = as_vec8<bf16x8>(make_uint4(lo_w[0], lo_w[1], lo_w[2], lo_w[3]));
+    bf16x8 ones;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt) {
         o[dt] = BF16::mfma(as_vec8<bf16x8>(vt[dt]), hi, START ? zero : o[dt]);
