@@ -31,7 +31,7 @@
 //     group g reads key 4g + sigma/4 (+16 for the second half of a 32-key block), head-dim elements
 //     16*(sigma%4) + 4*dt .. +3, so lane l's MFMA row stands for element 16*(l%16/4) + 4*dt + l%4 and
 //     each lane ends up owning output elements 16g .. 16g+15 of its query (32 contiguous bytes).
-// Loads of tile t+kRing-1 are issued while tile t is computed (ring of kRing tiles); completion is
+// Loads of tile t+1 are issued while tile t is computed (ring of two tiles); completion is
 // tracked with the vector-memory counter, one barrier per tile.  Measured: a ring of two (four
 // work-groups per CU) beats deeper rings, which cost resident wavefronts.
 //
@@ -49,14 +49,13 @@ namespace {
 
 constexpr int kHeadDim = 64;
 constexpr int kBN = 64;                 // keys per K/V tile
-// Work-group shape.  Measured on the dense layer (B=64, n=197) and the pruned batches: four
-// wavefronts with a ring of two tiles (32 KB, four work-groups per CU) is the fastest; deeper rings
-// (3, 4) lose resident wavefronts and gain nothing, eight-wavefront groups with rings of 2..4 tie
-// on dense batches and lose on short sequences.
-constexpr int kRing = 2;                // K/V tiles resident in LDS per work-group (2..4)
-constexpr int kAttnWaves = 4;           // wavefronts per work-group: 4 or 8 (the key-split and single-launch forms need 4)
+// Work-group shape.  Measured on the dense layer (B=64, n=197) and the pruned batches: four wavefronts with a ring of two
+// tiles (32 KB, four work-groups per CU) is the fastest; deeper rings (3, 4) lose resident wavefronts and gain nothing,
+// eight-wavefront groups tie on dense batches and lose on short sequences (577 tokens, B=32: 78 against 72 us).
+constexpr int kRing = 2;                // K/V tiles resident in LDS per work-group
+constexpr int kAttnWaves = 4;           // wavefronts per work-group
 constexpr int kAttnThreads = kWaveSize * kAttnWaves;
-constexpr int kAttnOcc = kAttnWaves == 8 ? 2 : (kRing == 2 ? 4 : (kRing == 3 ? 3 : 2));  // work-groups per CU aimed at
+constexpr int kAttnOcc = 4;             // work-groups per CU aimed at
 constexpr int kTileBytes = kBN * kHeadDim * 2;   // one K or one V tile: 8 KB
 // A sequence's LAST tile takes a tail of up to 16 keys along (n = 64k + 1 .. 64k + 16, k >= 2): 80 keys in one
 // pass instead of a pass of its own for a handful of keys -- ViT lengths are 64k + 1 before pruning (197, 577).
@@ -65,12 +64,17 @@ constexpr int kTileBytes = kBN * kHeadDim * 2;   // one K or one V tile: 8 KB
 // The tail's K rows and V rows live behind the ring.
 constexpr int kExtraRows = 16;
 constexpr int kExtraBytes = 2 * kExtraRows * kHeadDim * 2;   // K rows, then V rows: 4 KB
-constexpr bool kExtTail = kRing == 2;            // (the load bookkeeping of deeper rings does not count the tail's loads)
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLazyLog2 = 8.0f;       // probabilities stay below 2^8 between rescales
 constexpr int kSplitMaxGroups = 256;    // launches of at most this many 64-row q-tiles split the keys over the wavefronts
 constexpr int kMaxGatherTokens = 1536;  // tokens per image the gather-on-load variant can index in LDS
 constexpr int kMaxGridYZ = 65535;       // HIP's limit on the second and third grid dimension
+// Dispatch in phases (the order is described at the kernel).
+constexpr int kPhasePairs = 128;        // pairs of a dispatch batch
+constexpr int kPhaseTiles = 5;          // q-tiles of a phase; smaller bounds have one phase
+constexpr int kMaxPhases = 8;           // (phases grow where this many would not do)
+constexpr int kPhaseMinGroups = 2048;   // launches of fewer work-groups are not divided
+constexpr int kGroupBits = 10, kGroupMask = (1 << kGroupBits) - 1;
 
 // O^T += V^T P^T for one 32-key block: p[0..7] are this lane's probabilities (fp32).  The row sums
 // of P ride along on the matrix core: with an all-ones A operand every row of the result holds
@@ -313,6 +317,11 @@ __device__ __forceinline__ void tile_any(int rem, bool ext_tile, uint32_t tile0,
 //     at the end of the batch and retire while the real tiles are already running.
 //   * group * q_tiles is about what the chip holds resident, so in the dense case the q-tiles of a
 //     pair run together and their K/V re-reads hit L2 instead of going back to the fabric.
+// Long bounds go in phases: q-tiles 0 .. phase_tiles-1 of a batch of 128 pairs after the other, then the next phase_tiles of
+// every batch, and so on (grid (128, phase_tiles, phases * batches)).  With 577 tokens 512 pairs hold 9 MB of K/V per XCD,
+// more than its L2, so a whole batch per q-tile fetched K/V again for every q-tile: B=32 dense, bf16 / fp16 attention 80 / 69 us,
+// in phases 72 / 60; without the loads the arithmetic alone takes 62 / 50.  In one phase (each batch to its end) heavily pruned
+// launches start their work behind the surplus tiles of the batches in front (3 to 12 % slower at keep 0.1).
 //
 // A work-group has four wavefronts of 16 queries each.  Wavefront w issues the loads of rows
 // 16w .. 16w+15 of every K and V tile (four instructions per tile); rows past the end of the
@@ -353,9 +362,9 @@ struct StepArgs {
 //   through LDS at the end, each wavefront finishing four of the sixteen head-dim elements a lane owns.
 //   A sequence of up to 256 tokens then costs one tile time plus the merge instead of up to four.
 template <typename In, typename OutT, int MODE, bool SPLIT>
-__global__ __launch_bounds__(kAttnThreads, SPLIT ? 2 : (kAttnOcc < 1 ? 1 : kAttnOcc))
+__global__ __launch_bounds__(kAttnThreads, SPLIT ? 2 : kAttnOcc)
 void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H, uint32_t h_magic, int pairs,
-                 int group, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v, int tok32,
+                 int group_phase, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v, int tok32,
                  int tok_o32, const uint16_t* __restrict__ q, OutT* __restrict__ o, float scale_log2e,
                  int negate_q, StepArgs step) {
     // The parameters are ordered by when the kernel needs them: the first 14 dwords (up to tok_o32) are
@@ -372,16 +381,19 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
     static_assert(!SPLIT || kAttnWaves == 4, "the merge of the key-split form gives each of four wavefronts four elements");
     constexpr int WAVES = kAttnWaves;
     constexpr int kI = 8 / WAVES;                              // load instructions per wavefront per K (or V) tile
-    constexpr int kPer = 2 * kI;                               // ... per K+V tile
     constexpr int kBM = SPLIT ? 16 : 16 * WAVES;               // queries per work-group
-    constexpr bool EXT = kExtTail && !SPLIT;                   // a last tile may take a tail of <= 16 keys along
+    constexpr bool EXT = !SPLIT;                               // a last tile may take a tail of <= 16 keys along
     constexpr int kRingBytes = (SPLIT ? WAVES : kRing) * 2 * kTileBytes;
     __shared__ __attribute__((aligned(1024))) uint4 ring[(kRingBytes + (EXT ? kExtraBytes : 0)) / 16];   // [slot][K|V], tail rows
 
-    // grid (group, q_tiles, batches): work-groups are dispatched x-fastest, i.e. in the order
-    // (batch * q_tiles + m_tile) * group + slot of the mapping described above, with no division to undo it
-    const int m_tile = blockIdx.y;
-    const int pair = blockIdx.z * group + blockIdx.x;
+    // place in the order described above; all of it scalar arithmetic
+    const int group = group_phase & kGroupMask, phase_tiles = (int)((unsigned)group_phase >> kGroupBits);
+    int batch = blockIdx.z, m_tile = blockIdx.y;
+    if (phase_tiles != 0) {
+        const int batches = (pairs + kPhasePairs - 1) / kPhasePairs;
+        for (; batch >= batches; batch -= batches) m_tile += phase_tiles;
+    }
+    const int pair = batch * group + blockIdx.x;
     if (pair >= pairs) return;
     uint32_t img_u, h_u;
     divmod((uint32_t)pair, (uint32_t)H, h_magic, img_u, h_u);
@@ -419,7 +431,7 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
         // group m takes every q_tiles-th pass of the group over the tokens, the groups without rows of their own
         // (most of them, when much is pruned) included, before they leave
         const bool zero_fill = fill_mode == 1;
-        const int fill_groups = (int)gridDim.y;
+        const int fill_groups = phase_tiles == 0 ? (int)gridDim.y : (n_tok + phase_tiles * kBM - 1) / (phase_tiles * kBM) * phase_tiles;
         // kStep, q-tile 0 (with short sequences: the groups that have rows): the count of the kept tokens in front of
         // the image shares the barrier of the length count, so the group knows s and n together.  The other q-tiles
         // count it after the test that lets most of them leave.
@@ -521,25 +533,26 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
     const bool rides = EXT && n > 2 * kBN && tail_keys - 1u < (unsigned)kExtraRows;
     const int tiles = (int)(((unsigned)n + kBN - 1) / kBN) - (rides ? 1 : 0);
     const int ride_tile = rides ? tiles - 1 : -1;              // the tile that takes the tail along, if any
-    // Returns the number of load instructions issued (0 or kPer).  The per-lane offset is 32 bits wide:
-    // packed rows are addressed relative to the tile's first row (the 64-bit part is wave-uniform),
-    // gathered rows relative to the image's first token (the host checks that N tokens fit).
-    auto issue = [&](int t, int slot, bool may_ride = true) -> int {
+    // The per-lane offset is 32 bits wide: packed rows are addressed relative to the tile's first row (the 64-bit part is
+    // wave-uniform), gathered rows relative to the image's first token (the host checks that N tokens fit).
+    uint32_t voff_full[kI];                                    // packed rows of a tile whose 64 rows are all real (set below)
+    auto issue = [&](int t, int slot, auto full_tag, bool may_ride = true) {
+        constexpr bool FULL = decltype(full_tag)::value;       // tile t has 64 real rows and takes no tail along
         const int rem = n - t * kBN;
         const int need_rows = rem >= kBN ? kBN : 32 * ((rem + 31) >> 5);   // rows the tile's MFMAs touch
-        if (8 * kI * wave >= need_rows) return 0;
+        if (!FULL && 8 * kI * wave >= need_rows) return;
         const uint32_t dst = ring0 + slot * 2 * kTileBytes + wave * (1024 * kI);
         const int64_t tile_off = GATHER ? 0 : (int64_t)t * kBN * tok;
 #pragma unroll
         for (int i = 0; i < kI; ++i) {
             int rel = load_key + 8 * i;
-            rel = rel < rem ? rel : rem - 1;                    // past the end: the last real row again
+            if (!FULL) rel = rel < rem ? rel : rem - 1;         // past the end: the last real row again
             const uint32_t row = GATHER ? (uint32_t)idx_lds[t * kBN + rel] : (uint32_t)rel;
-            const uint32_t voff = row * tok_bytes + load_chunk;
+            const uint32_t voff = FULL && !GATHER ? voff_full[i] : row * tok_bytes + load_chunk;
             dma16(dst + i * 1024, voff, k_base + tile_off);
             dma16(dst + i * 1024 + kTileBytes, voff, v_base + tile_off);
         }
-        if (__builtin_expect(may_ride && t == ride_tile && wave < kExtraRows / 8, 0)) {
+        if (!FULL && __builtin_expect(may_ride && t == ride_tile && wave < kExtraRows / 8, 0)) {
             // the tail rows 64 .. 79 of a last tile: eight rows per instruction, wavefronts 0 and 1
             int rel = kBN + 8 * wave + (lane >> 3);
             rel = rel < rem ? rel : rem - 1;
@@ -548,7 +561,6 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
             dma16(extra0 + wave * 1024, voff, k_base + tile_off);
             dma16(extra0 + wave * 1024 + kExtraBytes / 2, voff, v_base + tile_off);
         }
-        return kPer;
     };
 
     // SPLIT: the whole tile t into this wavefront's own slot (eight instructions per operand)
@@ -570,14 +582,10 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
         }
     };
 
-    // c_next[d] = load instructions this wavefront has in flight for tile t+1+d (prologue: tiles 1 .. kRing-2)
-    int c_next[kRing > 2 ? kRing - 2 : 1] = {0};
     if (SPLIT) {
         if (wave < tiles) issue_own(wave);
     } else {
-        issue(0, 0, false);                                    // (a tile that takes a tail along is never the first)
-#pragma unroll
-        for (int d = 0; d < kRing - 2; ++d) c_next[d] = d + 1 < tiles ? issue(d + 1, d + 1) : 0;
+        issue(0, 0, std::false_type{}, false);                 // (a tile that takes a tail along is never the first)
     }
 
     // ---- Q: this lane's query row, head-dim elements 16g .. 16g+15 (zeros past the sequence end)
@@ -715,48 +723,46 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
         return;
     }
 
-    int slot = 0;                                              // ring slot of tile t
-    auto tile_step = [&](int t, auto first) {
-        // this wavefront's part of tile t has landed once only the later tiles' loads remain in flight
-        int behind = 0;
-#pragma unroll
-        for (int d = 0; d < kRing - 2; ++d) behind += c_next[d];
-        if (behind == 0) wait_vm<0>();
-        else if (behind == kPer) wait_vm<kPer>();
-        else if (behind == 2 * kPer) wait_vm<2 * kPer>();
-        else wait_vm<3 * kPer>();
-        __syncthreads();                    // tile t visible; every wavefront is past tile t-1's reads
-        const int slot_new = slot == 0 ? kRing - 1 : slot - 1; // slot of tile t-1, just freed, takes tile t+kRing-1
-        const int c_new = t + kRing - 1 < tiles ? issue(t + kRing - 1, slot_new) : 0;
-#pragma unroll
-        for (int d = 0; d + 1 < kRing - 2; ++d) c_next[d] = c_next[d + 1];
-        if (kRing > 2) c_next[kRing > 2 ? kRing - 3 : 0] = c_new;
-        if (wave_active)
-            tile_any<In, decltype(first)::value, EXT && !decltype(first)::value>(n - t * kBN, t == ride_tile,
-                                                      ring0 + slot * 2 * kTileBytes, extra0, k_rel0, v_rel0,
-                                                      q_frag, g, scale_log2e, m_run, l_acc, o_acc);
-        slot = slot == kRing - 1 ? 0 : slot + 1;
+    auto landed = [&]() {                   // a tile is visible, and every wavefront is past the reads of the one before
+        wait_vm<0>();
+        __syncthreads();
     };
+    int slot = 0;                           // ring slot of tile t
     if constexpr (PEEL) {
-        tile_step(0, std::true_type{});     // n > m0 >= 0: there is a first tile
-        for (int t = 1; t < tiles; ++t) tile_step(t, std::false_type{});
+        // The first tile, full ones, the last.  The loop in the middle knows only one form of a tile, so its accumulators stay
+        // in their registers; with the forms of all tail lengths inside the loop every tile ended in a dozen register copies
+        // that waited for its last products (577 tokens, B=32, bf16 / fp16 attention 72 -> 67 / 58 -> 56 us; 95 instead of
+        // 108 VGPRs).
+        landed();
+        if (tiles > 1) issue(1, 1, std::false_type{});
+        if (wave_active)
+            tile_any<In, true, false>(n, false, ring0, extra0, k_rel0, v_rel0, q_frag, g, scale_log2e, m_run, l_acc, o_acc);
+        if (tiles > 1) {
+            if (!GATHER)
+#pragma unroll
+                for (int i = 0; i < kI; ++i) voff_full[i] = (uint32_t)(load_key + 8 * i) * tok_bytes + load_chunk;
+            for (int t = 1; t < tiles - 1; ++t) {
+                slot ^= 1;
+                landed();
+                if (t + 1 < tiles - 1) issue(t + 1, slot ^ 1, std::true_type{});
+                else issue(t + 1, slot ^ 1, std::false_type{});
+                const uint32_t tile0 = ring0 + slot * 2 * kTileBytes;
+                if (wave_active)
+                    tile_update<In, 4, false, false>(tile0 + k_rel0, tile0 + (k_rel0 ^ 16u), tile0 + v_rel0, tile0 + (v_rel0 ^ 16u), 0, 0,
+                                                     q_frag, kBN, g, scale_log2e, m_run, l_acc, o_acc);
+            }
+            slot ^= 1;
+            landed();
+            if (wave_active)
+                tile_any<In, false, EXT>(n - (tiles - 1) * kBN, rides, ring0 + slot * 2 * kTileBytes, extra0, k_rel0, v_rel0,
+                                         q_frag, g, scale_log2e, m_run, l_acc, o_acc);
+        }
     } else {
-        // the same loop written out with the general tile form (see PEEL above: the code generator's schedule
-        // of the single-launch step depends on this exact shape)
+        // kStep: one loop with every form of a tile.  Its launches are mostly of short sequences, for which the code above is
+        // 4 to 6 % slower (B=32 dense 18.2 -> 18.9 us, B=128 at keep 0.5 32.2 -> 34.0 us; from nine tiles on it is 4 % faster).
         for (int t = 0; t < tiles; ++t) {
-            int behind = 0;
-#pragma unroll
-            for (int d = 0; d < kRing - 2; ++d) behind += c_next[d];
-            if (behind == 0) wait_vm<0>();
-            else if (behind == kPer) wait_vm<kPer>();
-            else if (behind == 2 * kPer) wait_vm<2 * kPer>();
-            else wait_vm<3 * kPer>();
-            __syncthreads();
-            const int slot_new = slot == 0 ? kRing - 1 : slot - 1;
-            const int c_new = t + kRing - 1 < tiles ? issue(t + kRing - 1, slot_new) : 0;
-#pragma unroll
-            for (int d = 0; d + 1 < kRing - 2; ++d) c_next[d] = c_next[d + 1];
-            if (kRing > 2) c_next[kRing > 2 ? kRing - 3 : 0] = c_new;
+            landed();
+            if (t + 1 < tiles) issue(t + 1, slot ^ 1, std::false_type{});
             if (wave_active) {
                 const int rem = n - t * kBN;
                 const uint32_t tile0 = ring0 + slot * 2 * kTileBytes;
@@ -776,8 +782,10 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
                     }
                 }
             }
+            // the x rows have long arrived: with several tiles the copy drains while the rest is computed
+            // (written out: as a call of store_packed_rows() the code generator schedules the whole kernel differently, fp16
+            // steps of B=32 to 128 2 to 6 % slower)
             if (t == 0) {
-                // the x rows have long arrived: with several tiles the copy drains while the rest is computed
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     const int j = m0 + 32 * i + (tid >> 3);
@@ -785,7 +793,7 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
                         reinterpret_cast<uint4*>(step.packed + ((int64_t)s + j) * tok + head_off)[tid & 7] = x_raw[i];
                 }
             }
-            slot = slot == kRing - 1 ? 0 : slot + 1;
+            slot ^= 1;
         }
     }
 
@@ -818,15 +826,30 @@ hipError_t launch_typed(const void* q, const void* k, const void* v, void* o,
     const int tile_rows = split ? 16 : 16 * kWaves;
     const int q_tiles = (max_seqlen + tile_rows - 1) / tile_rows;
     const int pairs8 = (pairs + kXcds - 1) / kXcds * kXcds;
-    const int group = pairs8 < kGroup ? pairs8 : kGroup;
-    const int batches = (pairs + group - 1) / group;
+    // Phases (see the kernel) where the bound allows more than kPhaseTiles q-tiles and the launch is more than the chip holds
+    // at once.  Up to 512 pairs the tiles of the first phase are few enough for the first of every pair to be among the 1024
+    // work-groups that start at once, which is all there is to do when much is pruned (577-token bound, B=32, keep 0.1: 4.9 us
+    // as before; 5.4 with five tiles); the modes with a mask, whose surplus groups have a mask to count, are not divided there
+    // (step of B=32, 577 tokens: keep 0.3 19.6 us undivided, 20.2 in phases).  Grids that phases would take past HIP's limits
+    // are not divided either, nor up to 512 pairs bounds of up to 512 tokens (40 x 330, fp16: 34.4 us dense becomes 32.4, but
+    // 4.2 at keep 0.1 becomes 4.7).
+    const int full_batches = (pairs + kPhasePairs - 1) / kPhasePairs;
+    const int first = full_batches > 4 ? kPhaseTiles : full_batches < 3 ? kPhaseTiles : full_batches == 3 ? 3 : 2;
+    const int phases = (q_tiles + first - 1) / first < kMaxPhases ? (q_tiles + first - 1) / first : kMaxPhases;
+    const int phase_tiles = (q_tiles + phases - 1) / phases;
+    const int64_t phase_batches = (int64_t)full_batches * phases;
+    const bool phased = !split && q_tiles > (full_batches > 4 ? kPhaseTiles : 8) && pairs > (MODE == kPacked ? kPhasePairs : kGroup) &&
+                        (int64_t)pairs * q_tiles > kPhaseMinGroups && phase_batches <= kMaxGridYZ &&
+                        phase_batches * kPhasePairs * phase_tiles <= INT32_MAX;
+    const int group = phased ? kPhasePairs : pairs8 < kGroup ? pairs8 : kGroup;
+    const int batches = phased ? (int)phase_batches : (pairs + group - 1) / group;
     if (q_tiles > kMaxGridYZ || batches > kMaxGridYZ || in_tok > INT32_MAX || out_tok > INT32_MAX)
         return hipErrorInvalidValue;                            // (the C ABI layer has refused these already)
     const hipError_t err = launch_kernel(split ? attn_kernel<In, OutT, MODE, true> : attn_kernel<In, OutT, MODE, false>,
-                       dim3(group, q_tiles, batches), dim3(kAttnThreads), stream,
+                       dim3(group, phased ? phase_tiles : q_tiles, batches), dim3(kAttnThreads), stream,
                        MODE == kPacked ? static_cast<const void*>(cu_seqlens) : static_cast<const void*>(keep),
-                       n_tok, fill_mode, H, div_magic((uint32_t)H), pairs, group, static_cast<const uint16_t*>(k),
-                       static_cast<const uint16_t*>(v), (int)in_tok, (int)out_tok, static_cast<const uint16_t*>(q),
+                       n_tok, fill_mode, H, div_magic((uint32_t)H), pairs, group | (phased ? phase_tiles : 0) << kGroupBits,
+                       static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), (int)in_tok, (int)out_tok, static_cast<const uint16_t*>(q),
                        static_cast<OutT*>(o), fabsf(scale) * kLog2e, scale < 0.f ? 1 : 0, step);
     return err;
 }

@@ -68,6 +68,18 @@ def test_loose_bound_many_surplus_q_tiles():
     check([40, 3, 70, 0, 129], 2, "f16", 4343, max_seqlen=64 * 300)
 
 
+@pytest.mark.parametrize("H,B,bound,dtype", [(3, 50, 1000, "f16"), (7, 47, 577, "bf16"), (11, 44, 577, "f16"), (13, 50, 330, "bf16"),
+                                             (9, 60, 385, "f16"), (5, 40, 6400, "f16")])
+def test_long_bounds_are_dispatched_in_phases(H, B, bound, dtype):
+    """More than 128 (image, head) pairs with a bound of many q-tiles: two, three, four and more batches of 128 pairs, the last
+    one partial, in two to eight phases whose last holds fewer q-tiles than the others.  Lengths from empty to the bound."""
+    assert B * H > 128 and B * H * ((bound + 63) // 64) > 2048
+    rng = np.random.default_rng(bound + H)
+    lengths = [int(v) for v in rng.integers(0, 90, size=B)]
+    lengths[0], lengths[B // 2], lengths[-1] = min(bound, 1000), min(bound, 1000) - 1, min(bound, 1000)
+    check(lengths, H, dtype, 5000 + bound, max_seqlen=bound)
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_last_tile_takes_a_tail_of_up_to_16_keys_along(dtype):
     """Large launches (not the key-split form) run a last tile of 65..80 keys in one pass when at least two full

@@ -105,6 +105,17 @@ def test_masks_beyond_16_kb():
     check(wl.Workload("b100w", 100, 197, 1, 64, "f16", 36, wl.keep_bernoulli(100, 197, 0.6, 13)), 0)
 
 
+@pytest.mark.parametrize("N,fill_mode,dtype", [(330, 1, torch.float16), (577, 0, torch.bfloat16), (577, 1, torch.float16)])
+def test_long_images_are_dispatched_in_phases(N, fill_mode, dtype):
+    """More than 512 (image, head) pairs of more than 320 tokens: q-tiles in phases, the zero fill shared by all of them."""
+    B, H = 58, 9
+    keep = wl.keep_bernoulli(B, N, 0.08, N)
+    keep[0] = 1
+    keep[5] = 0
+    keep[-1] = 1
+    check(wl.Workload("phases", B, N, H, 64, "f16", 40 + N, keep), fill_mode, dtype)
+
+
 def test_small_heads_and_odd_sizes():
     keep = wl.keep_bernoulli(7, 65, 0.5, 9)
     check(wl.Workload("odd", 7, 65, 1, 64, "f16", 33, keep), 0)
