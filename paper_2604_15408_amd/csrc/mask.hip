@@ -39,6 +39,8 @@ void token_scores_l2_kernel(const uint4* __restrict__ x, int64_t rows, int chunk
 // One work-group per (image, 32 tokens): eight lanes share a token and split the range of rivals
 // u = 1 .. N-1 between them (u = 1 + part, 9 + part, ...), so the counting loop is an eighth as long and
 // the image's scores are read from LDS; the eight partial counts meet in a three-step reduction.
+// The loop is bound by its 64-bit compares: rivals in front of the token are counted where they are not smaller, those behind
+// it (and itself) where they are larger, one compare each instead of two and a position test.
 constexpr int kTopkLanes = 8;
 constexpr int kTopkTokens = kBlockThreads / kTopkLanes;
 
@@ -52,12 +54,11 @@ void keep_topk_kernel(const double* __restrict__ scores, int N, int k, int chunk
     for (int u = threadIdx.x; u < N; u += kBlockThreads) s[u] = mine[u];
     __syncthreads();
     const double st = s[t < N ? t : 0];
-    int before = 0;
+    int before = 0, u = 1 + part;
 #pragma unroll 4
-    for (int u = 1 + part; u < N; u += kTopkLanes) {
-        const double su = s[u];
-        before += (u != t && (su > st || (su == st && u < t))) ? 1 : 0;
-    }
+    for (; u < t && u < N; u += kTopkLanes) before += s[u] >= st ? 1 : 0;
+#pragma unroll 4
+    for (; u < N; u += kTopkLanes) before += s[u] > st ? 1 : 0;
     before += __shfl_xor(before, 1, kWaveSize);
     before += __shfl_xor(before, 2, kWaveSize);
     before += __shfl_xor(before, 4, kWaveSize);
