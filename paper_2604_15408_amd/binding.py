@@ -79,6 +79,23 @@ def load() -> ctypes.CDLL:
     return _lib
 
 
+_marshal = None
+
+
+def _native():
+    """The native side of a checked call (native/marshal.cpp): tensor checks and the entry points with argument conversion."""
+    global _marshal
+    if _marshal is None:
+        load()
+        try:
+            from paper_2604_15408_amd import _ragged_marshal
+        except ImportError as e:
+            raise FileNotFoundError(f"{_PKG / '_ragged_marshal.so'} is missing or was built for another torch: build it with "
+                                    "`python -m paper_2604_15408_amd.build` (there is no fallback implementation)") from e
+        _marshal = _ragged_marshal
+    return _marshal
+
+
 def status_string(status: int) -> str:
     return load().ragged_status_string(int(status)).decode()
 
@@ -89,11 +106,17 @@ def version() -> int:
 
 def _stream(stream) -> int:
     if stream is None:
+        if torch.cuda.is_initialized():                         # the same stream without building a Stream object (0.3 of 1.1 us)
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _dev(t: torch.Tensor, name: str, dtype=None, shape=None) -> int:
+    p = (_marshal or _native()).dev(t, dtype, shape)
+    if p is not None:
+        return p
+    # something is wrong with the tensor, or it is not a plain one: the same checks with the argument's name
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a GPU tensor")
     if not t.is_contiguous():
@@ -123,7 +146,7 @@ def _pack_args(x, keep, packed, cu_seqlens, gather_idx, stream):
 def ragged_pack(x, keep, packed, cu_seqlens, gather_idx, stream=None) -> None:
     """x [B,N,C] f16/bf16, keep [B,N] uint8/bool -> packed [cap,C], cu_seqlens [B+1] i32,
     gather_idx [cap] i32 (all caller-allocated; cap = packed.shape[0])."""
-    _check("ragged_pack", load().ragged_pack(*_pack_args(x, keep, packed, cu_seqlens, gather_idx, stream)))
+    _check("ragged_pack", _native().ragged_pack(*_pack_args(x, keep, packed, cu_seqlens, gather_idx, stream)))
 
 
 def _attn_args(q, k, v, o, cu_seqlens, max_seqlen, scale, stream):
@@ -138,7 +161,7 @@ def _attn_args(q, k, v, o, cu_seqlens, max_seqlen, scale, stream):
 def ragged_attn(q, k, v, o, cu_seqlens, max_seqlen: int, scale: float, stream=None) -> None:
     """q,k,v [rows,H,D] f16/bf16 and o [rows,H,D] (same dtype or f32); only rows < cu_seqlens[-1]
     are read / written."""
-    _check("ragged_attn", load().ragged_attn(*_attn_args(q, k, v, o, cu_seqlens, max_seqlen, scale, stream)))
+    _check("ragged_attn", _native().ragged_attn(*_attn_args(q, k, v, o, cu_seqlens, max_seqlen, scale, stream)))
 
 
 def _token_rows(t: torch.Tensor, name: str, dtype, shape):
@@ -172,7 +195,7 @@ def ragged_attn_strided(q, k, v, o, cu_seqlens, max_seqlen: int, scale: float, s
     """ragged_attn on [rows,H,D] views with a token stride, e.g. the three slices of a fused
     [rows,3,H,D] QKV buffer; o may be a strided view too."""
     _check("ragged_attn_strided",
-           load().ragged_attn_strided(*_attn_strided_args(q, k, v, o, cu_seqlens, max_seqlen, scale, stream)))
+           _native().ragged_attn_strided(*_attn_strided_args(q, k, v, o, cu_seqlens, max_seqlen, scale, stream)))
 
 
 FLAG_SEQLEN_EXCEEDED = 1
@@ -182,7 +205,7 @@ def ragged_attn_checked(q, k, v, o, cu_seqlens, max_seqlen: int, scale: float, f
     """ragged_attn_strided that ORs FLAG_SEQLEN_EXCEEDED into flags[0] (int32 GPU tensor, zeroed by the caller)
     when some image holds more than max_seqlen tokens."""
     args = _attn_strided_args(q, k, v, o, cu_seqlens, max_seqlen, scale, stream)
-    _check("ragged_attn_checked", load().ragged_attn_checked(*args[:-1], _dev(flags, "flags", torch.int32), args[-1]))
+    _check("ragged_attn_checked", _native().ragged_attn_checked(*args[:-1], _dev(flags, "flags", torch.int32), args[-1]))
 
 
 def _repack_args(packed_in, keep_rows, cu_in, packed_out, cu_out, gather_out, stream):
@@ -201,7 +224,7 @@ def ragged_repack(packed_in, keep_rows, cu_in, packed_out, cu_out, gather_out, s
     """packed_in [cap_in,C], keep_rows [cap_in], cu_in [B+1] -> packed_out [cap_out,C], cu_out [B+1],
     gather_out [cap_out]: a second keep decision on packed rows."""
     _check("ragged_repack",
-           load().ragged_repack(*_repack_args(packed_in, keep_rows, cu_in, packed_out, cu_out, gather_out, stream)))
+           _native().ragged_repack(*_repack_args(packed_in, keep_rows, cu_in, packed_out, cu_out, gather_out, stream)))
 
 
 def _cls_args(packed, cu_seqlens, out, stream):
@@ -214,7 +237,7 @@ def _cls_args(packed, cu_seqlens, out, stream):
 
 def ragged_cls_extract(packed, cu_seqlens, out, stream=None) -> None:
     """out[i] = packed[cu_seqlens[i]] (first kept row of image i; zeros if the image has none)."""
-    _check("ragged_cls_extract", load().ragged_cls_extract(*_cls_args(packed, cu_seqlens, out, stream)))
+    _check("ragged_cls_extract", _native().ragged_cls_extract(*_cls_args(packed, cu_seqlens, out, stream)))
 
 
 def _attn_padded_args(q, k, v, o, keep, scale, fill_mode, stream):
@@ -228,7 +251,7 @@ def _attn_padded_args(q, k, v, o, keep, scale, fill_mode, stream):
 def ragged_attn_padded(q, k, v, o, keep, scale: float, fill_mode: int = 0, stream=None) -> None:
     """q,k,v,o [B,N,H,D], keep [B,N]: pack + attention + unpack of one layer in a single launch."""
     _check("ragged_attn_padded",
-           load().ragged_attn_padded(*_attn_padded_args(q, k, v, o, keep, scale, fill_mode, stream)))
+           _native().ragged_attn_padded(*_attn_padded_args(q, k, v, o, keep, scale, fill_mode, stream)))
 
 
 def _step_args(x, keep, q, k, v, packed, cu_seqlens, gather_idx, o, out, scale, fill_mode, stream):
@@ -246,7 +269,7 @@ def ragged_pack_attn_unpack(x, keep, q, k, v, packed, cu_seqlens, gather_idx, o,
                             fill_mode: int = 0, stream=None) -> None:
     """ragged_pack(x, keep) + ragged_attn(q, k, v) + ragged_unpack(o -> out) in one launch; q, k, v,
     o, packed, gather_idx hold cap >= B*N rows."""
-    _check("ragged_pack_attn_unpack", load().ragged_pack_attn_unpack(
+    _check("ragged_pack_attn_unpack", _native().ragged_pack_attn_unpack(
         *_step_args(x, keep, q, k, v, packed, cu_seqlens, gather_idx, o, out, scale, fill_mode, stream)))
 
 
@@ -281,7 +304,7 @@ def ragged_linear(x, w, bias, residual, y, rows_dev=None, act: str = "none", str
     """y = act(x @ w.T + bias) + residual over the first min(rows, *rows_dev) rows.  x [rows,K], w [N,K].
     rows_hint: an estimate of *rows_dev known on the host (0 = rows); it only picks the launch shape."""
     _check("ragged_linear",
-           load().ragged_linear(*_linear_args(x, w, bias, residual, y, rows_dev, act, stream, rows_hint)))
+           _native().ragged_linear(*_linear_args(x, w, bias, residual, y, rows_dev, act, stream, rows_hint)))
 
 
 def prepare_linear(x, w, bias, residual, y, rows_dev=None, act: str = "none", stream=None,
@@ -300,7 +323,7 @@ def _layernorm_args(x, gamma, beta, y, rows_dev, eps, stream):
 
 def ragged_layernorm(x, gamma, beta, y, rows_dev=None, eps: float = 1e-6, stream=None) -> None:
     """Row-wise LayerNorm of x [rows,C] into y over the first min(rows, *rows_dev) rows."""
-    _check("ragged_layernorm", load().ragged_layernorm(*_layernorm_args(x, gamma, beta, y, rows_dev, eps, stream)))
+    _check("ragged_layernorm", _native().ragged_layernorm(*_layernorm_args(x, gamma, beta, y, rows_dev, eps, stream)))
 
 
 def prepare_layernorm(x, gamma, beta, y, rows_dev=None, eps: float = 1e-6, stream=None) -> "Prepared":
@@ -311,7 +334,7 @@ def prepare_layernorm(x, gamma, beta, y, rows_dev=None, eps: float = 1e-6, strea
 def ragged_token_scores_l2(x, scores, stream=None) -> None:
     """scores[b, t] = squared l2 norm of x[b, t, :] (fp64).  x [B,N,C] f16/bf16, scores [B,N] float64."""
     B, N, C = x.shape
-    _check("ragged_token_scores_l2", load().ragged_token_scores_l2(
+    _check("ragged_token_scores_l2", _native().ragged_token_scores_l2(
         _dev(x, "x", (torch.float16, torch.bfloat16)), B * N, C, _DTYPE_CODE[x.dtype],
         _dev(scores, "scores", torch.float64, (B, N)), _stream(stream)))
 
@@ -319,7 +342,7 @@ def ragged_token_scores_l2(x, scores, stream=None) -> None:
 def ragged_keep_topk(scores, k: int, keep, stream=None) -> None:
     """keep[b] = token 0 plus the k-1 highest-scoring other tokens of image b (ties: lower position)."""
     B, N = scores.shape
-    _check("ragged_keep_topk", load().ragged_keep_topk(
+    _check("ragged_keep_topk", _native().ragged_keep_topk(
         _dev(scores, "scores", torch.float64), B, N, int(k), _dev(keep, "keep", (torch.uint8, torch.bool), (B, N)),
         _stream(stream)))
 
@@ -337,7 +360,7 @@ def ragged_unpack(src, keep, cu_seqlens, gather_idx, out, fill_mode: int, stream
     """src [rows,C] -> out [B,N,C].  fill_mode 0 needs gather_idx (keep may be None); fill_mode 1
     needs keep (gather_idx may be None)."""
     _check("ragged_unpack",
-           load().ragged_unpack(*_unpack_args(src, keep, cu_seqlens, gather_idx, out, fill_mode, stream)))
+           _native().ragged_unpack(*_unpack_args(src, keep, cu_seqlens, gather_idx, out, fill_mode, stream)))
 
 
 _UNTYPED = None
@@ -413,4 +436,4 @@ def prepare_unpack(src, keep, cu_seqlens, gather_idx, out, fill_mode: int, strea
 
 
 def ragged_noop(grid: int, stream=None) -> None:
-    _check("ragged_noop", load().ragged_noop(int(grid), _stream(stream)))
+    _check("ragged_noop", _native().ragged_noop(int(grid), _stream(stream)))

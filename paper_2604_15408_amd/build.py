@@ -69,9 +69,32 @@ def build(verbose: bool = False, extra_flags=()) -> Path:
     if res.returncode != 0:
         raise RuntimeError(f"link failed:\n{res.stderr}")
     os.replace(tmp, LIB)
+    build_marshal()
     build_call_cost(hipcc)
     build_ceilings(hipcc)
     return LIB
+
+
+MARSHAL = PKG / "_ragged_marshal.so"
+
+
+def build_marshal() -> Path:
+    """The binding's native side (native/marshal.cpp): a Python extension against the installed torch and the C ABI."""
+    import sysconfig
+
+    import torch
+    t = Path(torch.__file__).resolve().parent
+    tmp = MARSHAL.with_suffix(f".tmp{os.getpid()}.so")
+    res = subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+                          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", f"-I{ROOT / 'include'}",
+                          f"-I{t / 'include'}", f"-I{t / 'include' / 'torch' / 'csrc' / 'api' / 'include'}",
+                          f"-I{sysconfig.get_paths()['include']}", "-o", str(tmp), str(PKG / "native" / "marshal.cpp"),
+                          f"-L{PKG}", "-lragged_hip", f"-L{t / 'lib'}", "-lc10", "-ltorch_cpu", "-ltorch_python",
+                          "-Wl,-rpath,$ORIGIN"], capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"building _ragged_marshal.so failed:\n{res.stderr}")
+    os.replace(tmp, MARSHAL)
+    return MARSHAL
 
 
 CALL_COST = PKG / "ragged_call_cost"

@@ -206,3 +206,32 @@ def test_binding_refuses_cpu_tensors():
     with pytest.raises(TypeError):
         binding.ragged_pack(x, torch.ones(1, 4, dtype=torch.uint8), torch.zeros(4, 64, dtype=torch.float16),
                             torch.zeros(2, dtype=torch.int32), torch.zeros(4, dtype=torch.int32), stream=0)
+
+
+def test_native_entry_points_return_what_ctypes_returns(lib):
+    """The binding's native side passes every kind of argument on as ctypes does: pointers and None, integers (wrapped to the
+    parameter's width), floats; a wrong number or kind of arguments is a TypeError and nothing is called."""
+    native = binding._native()
+    for name in binding.EXPORTS:
+        fn = getattr(lib, name)
+        if fn.restype is not ctypes.c_int or name == "ragged_version":
+            continue
+        n = len(fn.argtypes)
+        for args in (tuple(None if t is ctypes.c_void_p else 0 for t in fn.argtypes),
+                     tuple(FAKE if t is ctypes.c_void_p else -1 for t in fn.argtypes),
+                     tuple(FAKE if t is ctypes.c_void_p else 1.5 if t is ctypes.c_float else (1 << 32) for t in fn.argtypes)):
+            status = getattr(native, name)(*args)
+            assert status == fn(*args) and status != 0, (name, args)
+        with pytest.raises(TypeError):
+            getattr(native, name)(*args[:-1])
+        with pytest.raises(TypeError):
+            getattr(native, name)(*(["x"] * n))
+
+
+def test_native_check_leaves_other_tensors_to_the_python_checks(lib):
+    import torch
+    native = binding._native()
+    for t in (torch.zeros(2, 3), torch.nn.Parameter(torch.zeros(2)), torch.zeros(0), None, 3, "x"):
+        assert native.dev(t, None, None) is None
+    with pytest.raises(TypeError, match="x must be a GPU tensor"):
+        binding._dev(torch.zeros(2, 3), "x")

@@ -257,3 +257,30 @@ def test_steps_on_three_streams_fill_every_buffer_set():
         for n in ("packed", "o"):
             assert torch.equal(getattr(p, n)[:T].view(torch.int16), getattr(ref, n)[:T].view(torch.int16)), n
         assert torch.equal(p.out.view(torch.int16), ref.out.view(torch.int16))
+
+
+def test_checked_calls_refuse_what_they_refused():
+    """The checks of a tensor argument run in native code and are repeated in Python for the message: type, strides, dtype (one
+    or several allowed) and shape, for plain tensors, views, parameters and subclasses, on the current stream."""
+    x = torch.zeros(2, 3, 8, dtype=torch.float16, device=DEV)
+    dev = binding._dev
+    f16 = torch.float16
+    assert dev(x, "x") == dev(x, "x", f16, (2, 3, 8)) == dev(x, "x", (torch.bfloat16, f16), x.shape) == x.data_ptr()
+    assert dev(x[1], "x", f16, (3, 8)) == x.data_ptr() + 48
+    assert dev(torch.nn.Parameter(x, requires_grad=False), "x", f16) == x.data_ptr()
+
+    class Sub(torch.Tensor):
+        pass
+    assert dev(x.as_subclass(Sub), "x", f16, (2, 3, 8)) == x.data_ptr()
+    for bad, error in ((x[:, :, ::2], ValueError), (x.transpose(0, 1), ValueError), (x.float(), TypeError), (x.cpu(), TypeError),
+                       (x[:1], ValueError), (x.view(2, 24), ValueError), (None, TypeError)):
+        with pytest.raises(error, match="^x "):
+            dev(bad, "x", f16, (2, 3, 8))
+    with pytest.raises(TypeError, match="^x "):
+        dev(x, "x", (torch.uint8, torch.bool))
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert binding._stream(None) == side.cuda_stream
+    assert binding._stream(None) == torch.cuda.current_stream().cuda_stream
+    with pytest.raises(Exception):
+        torch.vmap(lambda t: (dev(t, "x"), t)[1])(x)
