@@ -118,14 +118,15 @@ void layernorm_kernel(const uint16_t* x, const uint16_t* __restrict__ gamma,    
 // first operands): both fitted to single-round launches at 768-wide layers, K = 768 and 3072, fp16.  Large tiles need
 // the fewest operand bytes per product, small ones fill the chip when rows are few, and the heights in between are there
 // because a round is paid whole: 12 544 x 768 x 3072 takes 52 us in 237 tiles of 160 rows, 61 in 147 of 256 rows; 1334 x
-// 2304 x 768 takes 8.9 in 252 tiles of 96 x 128, 11.9 in 378 of 64 x 128, 15 in 81 of 160 x 256.
+// 2304 x 768 takes 8.9 in 252 tiles of 96 x 128, 11.9 in 378 of 64 x 128, 15 in 81 of 160 x 256; 200 x 768 x 3072 takes 11.4 in
+// 84 tiles of 32 x 64, 12.8 in 48 of 64 x 64 (a CU draws its operands at about 87 GB/s, so fewer bytes per CU is less time).
 constexpr int kCus = 256;
 constexpr int kGeluNs = 80;                                    // per nj * mt
 struct TileShape { int nj, mt, step_ns, tile_ns; };
 constexpr TileShape kTileShapes[] = {
     {8, 8, 1040, 6000}, {8, 7, 900, 5800}, {8, 6, 800, 5300}, {8, 5, 670, 4700}, {8, 4, 580, 3300},
     {6, 4, 475, 2600}, {6, 3, 410, 1700}, {6, 2, 385, 1000}, {4, 4, 375, 1600}, {4, 3, 340, 1100},
-    {4, 2, 300, 600}, {2, 4, 290, 800}, {2, 2, 235, 600}};
+    {4, 2, 300, 600}, {2, 4, 290, 800}, {2, 2, 235, 600}, {2, 1, 180, 500}};
 // Feature tiles per panel: the 32 CUs of an XCD then work on a patch of about 6 x 5 tiles, which pulls fewest operand
 // bytes into its L2 (12 544 x 3072 x 768: 78 -> 72.5 us against whole rows of tiles; widths of 4 to 6 are alike).
 constexpr int kPanel = 6;

@@ -440,7 +440,7 @@ void linear_kernel(LinearArgs p) {
 }
 
 // The tile shapes there are, as {NJ, MT}: 32 NJ features x 32 MT tokens.
-#define LINEAR_SHAPES(X) X(8, 8) X(8, 7) X(8, 6) X(8, 5) X(8, 4) X(6, 4) X(6, 3) X(6, 2) X(4, 4) X(4, 3) X(4, 2) X(2, 4) X(2, 2)
+#define LINEAR_SHAPES(X) X(8, 8) X(8, 7) X(8, 6) X(8, 5) X(8, 4) X(6, 4) X(6, 3) X(6, 2) X(4, 4) X(4, 3) X(4, 2) X(2, 4) X(2, 2) X(2, 1)
 
 template <typename In>
 hipError_t launch_linear_tile(int nj, int mt, int groups, const LinearArgs& args, hipStream_t stream) {

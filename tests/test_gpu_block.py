@@ -92,7 +92,7 @@ def test_linear_every_launch_shape(dtype, act, residual):
     (3600, 4096, 64), (3100, 4096, 128), (3400, 3072, 128), (2100, 4096, 256), (2700, 2304, 128),   # 256 features x 256 .. 128 rows
     (3100, 1536, 192), (5500, 576, 64), (1800, 1152, 64),                                           # 192 features x 128, 96, 64 rows
     (2700, 1152, 128), (4100, 512, 64), (900, 1152, 64),                                            # 128 features x 128, 96, 64 rows
-    (1800, 576, 64), (100, 64, 64)])                                                                # 64 features x 128, 64 rows
+    (1800, 576, 64), (9000, 64, 64), (100, 64, 64), (300, 128, 1024)])                              # 64 features x 128, 64, 32 rows
 def test_linear_every_tile_shape(hint, N, K):
     """Each tile shape (picked through the row estimate) at row counts that end just before, on and just behind a tile
     edge; one k-step, fewer and more k-steps than the LDS ring has stages; several tiles per work-group."""
