@@ -25,16 +25,12 @@ HIPCC_FLAGS = [
 ]
 
 
-# linear.hip: keep MFMA results in plain VGPRs.  Where LDS use limits a CU to one work-group the
-# compiler otherwise moves accumulators to AGPRs and copies them back and forth around every MFMA.
-#
-# The short kernels (attention, pack / unpack, mask producer): the first 14 dwords of a kernel's arguments arrive in scalar registers with the
-# wavefront instead of being fetched by its first instructions (the attention kernel orders its parameters
-# by first use).  Measured side by side: attention and the 36-kernel pipeline 2-3 % faster; the linear
-# layers, whose launches last 8-90 us, 1-2 % slower with it, so they are built without.
+# The first 14 dwords of a kernel's arguments arrive in scalar registers with the wavefront instead of being fetched by its first
+# instructions (attention and the linear layers order their parameters by first use).  Measured side by side: attention and the
+# 36-kernel pipeline 2-3 % faster, linear layers over a few hundred to some thousand rows 1-2 %.
 PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=14"]
-PER_FILE_FLAGS = {"attn.hip": PRELOAD, "pack_unpack.hip": PRELOAD,
-                  "mask.hip": PRELOAD}
+PER_FILE_FLAGS = {"attn.hip": PRELOAD, "pack_unpack.hip": PRELOAD, "mask.hip": PRELOAD, "linear_f16.hip": PRELOAD,
+                  "linear_bf16.hip": PRELOAD}
 
 
 def _hipcc() -> str:
