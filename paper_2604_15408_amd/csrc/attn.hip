@@ -74,7 +74,6 @@ constexpr int kPhasePairs = 128;        // pairs of a dispatch batch
 constexpr int kPhaseTiles = 5;          // q-tiles of a phase; smaller bounds have one phase
 constexpr int kMaxPhases = 8;           // (phases grow where this many would not do)
 constexpr int kPhaseMinGroups = 2048;   // launches of fewer work-groups are not divided
-constexpr int kGroupBits = 10, kGroupMask = (1 << kGroupBits) - 1;
 
 // O^T += V^T P^T for one 32-key block: p[0..7] are this lane's probabilities (fp32).  The row sums
 // of P ride along on the matrix core: with an all-ones A operand every row of the result holds
@@ -387,11 +386,12 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
     __shared__ __attribute__((aligned(1024))) uint4 ring[(kRingBytes + (EXT ? kExtraBytes : 0)) / 16];   // [slot][K|V], tail rows
 
     // place in the order described above; all of it scalar arithmetic
-    const int group = group_phase & kGroupMask, phase_tiles = (int)((unsigned)group_phase >> kGroupBits);
-    int batch = blockIdx.z, m_tile = blockIdx.y;
-    if (phase_tiles != 0) {
-        const int batches = (pairs + kPhasePairs - 1) / kPhasePairs;
+    int batch = blockIdx.z, m_tile = blockIdx.y, group = group_phase;
+    const int phase_tiles = -group_phase;                      // > 0: a launch in phases
+    if (__builtin_expect(phase_tiles > 0, 0)) {
+        const int batches = (int)((unsigned)(pairs + kPhasePairs - 1) / kPhasePairs);
         for (; batch >= batches; batch -= batches) m_tile += phase_tiles;
+        group = kPhasePairs;
     }
     const int pair = batch * group + blockIdx.x;
     if (pair >= pairs) return;
@@ -431,7 +431,7 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
         // group m takes every q_tiles-th pass of the group over the tokens, the groups without rows of their own
         // (most of them, when much is pruned) included, before they leave
         const bool zero_fill = fill_mode == 1;
-        const int fill_groups = phase_tiles == 0 ? (int)gridDim.y : (n_tok + phase_tiles * kBM - 1) / (phase_tiles * kBM) * phase_tiles;
+        const int fill_groups = phase_tiles < 0 ? (int)gridDim.y : (n_tok + phase_tiles * kBM - 1) / (phase_tiles * kBM) * phase_tiles;
         // kStep, q-tile 0 (with short sequences: the groups that have rows): the count of the kept tokens in front of
         // the image shares the barrier of the length count, so the group knows s and n together.  The other q-tiles
         // count it after the test that lets most of them leave.
@@ -535,24 +535,22 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
     const int ride_tile = rides ? tiles - 1 : -1;              // the tile that takes the tail along, if any
     // The per-lane offset is 32 bits wide: packed rows are addressed relative to the tile's first row (the 64-bit part is
     // wave-uniform), gathered rows relative to the image's first token (the host checks that N tokens fit).
-    uint32_t voff_full[kI];                                    // packed rows of a tile whose 64 rows are all real (set below)
-    auto issue = [&](int t, int slot, auto full_tag, bool may_ride = true) {
-        constexpr bool FULL = decltype(full_tag)::value;       // tile t has 64 real rows and takes no tail along
+    auto issue = [&](int t, int slot, bool may_ride = true) {
         const int rem = n - t * kBN;
         const int need_rows = rem >= kBN ? kBN : 32 * ((rem + 31) >> 5);   // rows the tile's MFMAs touch
-        if (!FULL && 8 * kI * wave >= need_rows) return;
+        if (8 * kI * wave >= need_rows) return;
         const uint32_t dst = ring0 + slot * 2 * kTileBytes + wave * (1024 * kI);
         const int64_t tile_off = GATHER ? 0 : (int64_t)t * kBN * tok;
 #pragma unroll
         for (int i = 0; i < kI; ++i) {
             int rel = load_key + 8 * i;
-            if (!FULL) rel = rel < rem ? rel : rem - 1;         // past the end: the last real row again
+            rel = rel < rem ? rel : rem - 1;                    // past the end: the last real row again
             const uint32_t row = GATHER ? (uint32_t)idx_lds[t * kBN + rel] : (uint32_t)rel;
-            const uint32_t voff = FULL && !GATHER ? voff_full[i] : row * tok_bytes + load_chunk;
+            const uint32_t voff = row * tok_bytes + load_chunk;
             dma16(dst + i * 1024, voff, k_base + tile_off);
             dma16(dst + i * 1024 + kTileBytes, voff, v_base + tile_off);
         }
-        if (!FULL && __builtin_expect(may_ride && t == ride_tile && wave < kExtraRows / 8, 0)) {
+        if (__builtin_expect(may_ride && t == ride_tile && wave < kExtraRows / 8, 0)) {
             // the tail rows 64 .. 79 of a last tile: eight rows per instruction, wavefronts 0 and 1
             int rel = kBN + 8 * wave + (lane >> 3);
             rel = rel < rem ? rel : rem - 1;
@@ -585,7 +583,7 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
     if (SPLIT) {
         if (wave < tiles) issue_own(wave);
     } else {
-        issue(0, 0, std::false_type{}, false);                 // (a tile that takes a tail along is never the first)
+        issue(0, 0, false);                                    // (a tile that takes a tail along is never the first)
     }
 
     // ---- Q: this lane's query row, head-dim elements 16g .. 16g+15 (zeros past the sequence end)
@@ -734,18 +732,14 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
         // that waited for its last products (577 tokens, B=32, bf16 / fp16 attention 72 -> 67 / 58 -> 56 us; 95 instead of
         // 108 VGPRs).
         landed();
-        if (tiles > 1) issue(1, 1, std::false_type{});
+        if (tiles > 1) issue(1, 1);
         if (wave_active)
             tile_any<In, true, false>(n, false, ring0, extra0, k_rel0, v_rel0, q_frag, g, scale_log2e, m_run, l_acc, o_acc);
         if (tiles > 1) {
-            if (!GATHER)
-#pragma unroll
-                for (int i = 0; i < kI; ++i) voff_full[i] = (uint32_t)(load_key + 8 * i) * tok_bytes + load_chunk;
             for (int t = 1; t < tiles - 1; ++t) {
                 slot ^= 1;
                 landed();
-                if (t + 1 < tiles - 1) issue(t + 1, slot ^ 1, std::true_type{});
-                else issue(t + 1, slot ^ 1, std::false_type{});
+                issue(t + 1, slot ^ 1);
                 const uint32_t tile0 = ring0 + slot * 2 * kTileBytes;
                 if (wave_active)
                     tile_update<In, 4, false, false>(tile0 + k_rel0, tile0 + (k_rel0 ^ 16u), tile0 + v_rel0, tile0 + (v_rel0 ^ 16u), 0, 0,
@@ -762,7 +756,7 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
         // 4 to 6 % slower (B=32 dense 18.2 -> 18.9 us, B=128 at keep 0.5 32.2 -> 34.0 us; from nine tiles on it is 4 % faster).
         for (int t = 0; t < tiles; ++t) {
             landed();
-            if (t + 1 < tiles) issue(t + 1, slot ^ 1, std::false_type{});
+            if (t + 1 < tiles) issue(t + 1, slot ^ 1);
             if (wave_active) {
                 const int rem = n - t * kBN;
                 const uint32_t tile0 = ring0 + slot * 2 * kTileBytes;
@@ -848,7 +842,7 @@ hipError_t launch_typed(const void* q, const void* k, const void* v, void* o,
     const hipError_t err = launch_kernel(split ? attn_kernel<In, OutT, MODE, true> : attn_kernel<In, OutT, MODE, false>,
                        dim3(group, phased ? phase_tiles : q_tiles, batches), dim3(kAttnThreads), stream,
                        MODE == kPacked ? static_cast<const void*>(cu_seqlens) : static_cast<const void*>(keep),
-                       n_tok, fill_mode, H, div_magic((uint32_t)H), pairs, group | (phased ? phase_tiles : 0) << kGroupBits,
+                       n_tok, fill_mode, H, div_magic((uint32_t)H), pairs, phased ? -phase_tiles : group,
                        static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), (int)in_tok, (int)out_tok, static_cast<const uint16_t*>(q),
                        static_cast<OutT*>(o), fabsf(scale) * kLog2e, scale < 0.f ? 1 : 0, step);
     return err;
