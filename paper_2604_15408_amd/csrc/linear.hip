@@ -3,7 +3,7 @@
 // number of kept tokens), for gfx950.
 //
 // The linear kernel itself is in linear_kernel.h (instantiated per input type in linear_f16.hip and linear_bf16.hip); this
-// file picks its tile shape and holds LayerNorm.
+// file launches it in the shape that linear_walk.h picks and holds LayerNorm.
 //
 // layernorm_kernel: one wavefront per row, the row held in registers, two passes (mean, then the
 //   biased variance of the centred values) in fp32.
@@ -110,50 +110,18 @@ void layernorm_kernel(const uint16_t* x, const uint16_t* __restrict__ gamma,    
     }
 }
 
-
-// Tile shape.  The kernel runs one work-group per CU and hands the tiles out evenly, so a call takes
-//     ceil(tiles / 256) * (k-steps * step_ns + tile_ns [+ GELU]),
-// and the shape with the least of it is taken (rows: the caller's estimate, or the capacity).  step_ns is what a step of
-// 64 k costs a CU (arithmetic and LDS traffic of the tile plus one barrier), tile_ns what a tile costs besides (epilogue,
-// first operands): both fitted to single-round launches at 768-wide layers, K = 768 and 3072, fp16.  Large tiles need
-// the fewest operand bytes per product, small ones fill the chip when rows are few, and the heights in between are there
-// because a round is paid whole: 12 544 x 768 x 3072 takes 52 us in 237 tiles of 160 rows, 61 in 147 of 256 rows; 1334 x
-// 2304 x 768 takes 8.9 in 252 tiles of 96 x 128, 11.9 in 378 of 64 x 128, 15 in 81 of 160 x 256; 200 x 768 x 3072 takes 11.4 in
-// 84 tiles of 32 x 64, 12.8 in 48 of 64 x 64 (a CU draws its operands at about 87 GB/s, so fewer bytes per CU is less time).
-constexpr int kCus = 256;
-constexpr int kGeluNs = 80;                                    // per nj * mt
-struct TileShape { int nj, mt, step_ns, tile_ns; };
-constexpr TileShape kTileShapes[] = {
-    {8, 8, 1040, 6000}, {8, 7, 900, 5800}, {8, 6, 800, 5300}, {8, 5, 670, 4700}, {8, 4, 580, 3300},
-    {6, 4, 475, 2600}, {6, 3, 410, 1700}, {6, 2, 385, 1000}, {4, 4, 375, 1600}, {4, 3, 340, 1100},
-    {4, 2, 300, 600}, {2, 4, 290, 800}, {2, 2, 235, 600}, {2, 1, 180, 500}};
-// Feature tiles per panel: the 32 CUs of an XCD then work on a patch of about 6 x 5 tiles, which pulls fewest operand
-// bytes into its L2 (12 544 x 3072 x 768: 78 -> 72.5 us against whole rows of tiles; widths of 4 to 6 are alike).
-constexpr int kPanel = 6;
-
 }  // namespace
 
 hipError_t launch_linear(const void* x, const void* w, const void* bias, const void* res, void* y, int rows_cap,
                          const int32_t* rows_dev, int rows_hint, int N, int K, int act, ragged_dtype dt,
                          hipStream_t stream) {
-    int nj = 2, mt = 2;                                        // N is a multiple of 64: this one always fits
-    int64_t best = INT64_MAX;
-    for (const TileShape& c : kTileShapes) {
-        if (N % (32 * c.nj) != 0) continue;
-        const int64_t tiles = (int64_t)((rows_hint + 32 * c.mt - 1) / (32 * c.mt)) * (N / (32 * c.nj));
-        const int64_t cost = (tiles + kCus - 1) / kCus * (K / kTK * c.step_ns + c.tile_ns + (act == 1 ? kGeluNs * c.nj * c.mt : 0));
-        if (cost < best) { best = cost; nj = c.nj; mt = c.mt; }
-    }
-    const int n_tiles = N / (32 * nj);
-    const int panels = (n_tiles + kPanel - 1) / kPanel;
-    const int panel = (n_tiles + panels - 1) / panels;
-    const int last = n_tiles - (n_tiles - 1) / panel * panel;
-    const int64_t tiles = (int64_t)((rows_cap + 32 * mt - 1) / (32 * mt)) * n_tiles;
-    const int groups = (int)(tiles < kCus ? (tiles + kXcds - 1) / kXcds * kXcds : kCus);
+    const TileShape c = pick_linear_shape(rows_hint, N, K, act);
+    const LinearGrid g(c.nj, c.mt, rows_cap, N);
     const LinearArgs args{static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w), static_cast<const uint16_t*>(bias),
-                          static_cast<const uint16_t*>(res), static_cast<uint16_t*>(y), rows_dev, rows_cap, N, K, act, n_tiles,
-                          panel, div_magic((uint32_t)panel), div_magic((uint32_t)last)};
-    return dt == RAGGED_F16 ? launch_linear_f16(nj, mt, groups, args, stream) : launch_linear_bf16(nj, mt, groups, args, stream);
+                          static_cast<const uint16_t*>(res), static_cast<uint16_t*>(y), rows_dev, rows_cap, N, K, act, g.n_tiles,
+                          g.panel, div_magic((uint32_t)g.panel), div_magic((uint32_t)g.last)};
+    return dt == RAGGED_F16 ? launch_linear_f16(c.nj, c.mt, g.groups, args, stream)
+                            : launch_linear_bf16(c.nj, c.mt, g.groups, args, stream);
 }
 
 int layernorm_max_width() { return kWaveSize * kLnChunks * 8; }

@@ -1,5 +1,5 @@
 // linear_kernel: y[m][n] = act( sum_k x[m][k] * w[n][k] + bias[n] ) (+ residual[m][n]) over packed rows, on MFMA
-// (internal; the rule that picks a tile shape is in linear.hip, one source per input type instantiates the kernel).
+// (internal; the rule that picks a tile shape and the walk over the tiles are in linear_walk.h, one source per input type instantiates the kernel).
 //
 // x [rows, K], w [N, K]: both operands are contiguous along k, which is how an MFMA lane wants them (8 consecutive k per
 // 16-byte read).  The product is formed transposed (features x tokens: w is the A operand), and MFMA row m' of feature
@@ -38,13 +38,13 @@
 
 #include "common.h"
 #include "linear_epilogue.h"
+#include "linear_walk.h"
 #include "mfma_lds.h"
 
 namespace ragged {
 
-constexpr int kTK = 64;                          // contraction elements per step: 128-byte LDS rows
 constexpr int kLinWaves = 4;                     // one wavefront per SIMD
-constexpr int kLdsBytes = 160 * 1024;
+static_assert(kLinearXcds == kXcds, "tiles are dealt out per XCD");
 
 struct LinearArgs {
     const uint16_t* x;
@@ -55,7 +55,7 @@ struct LinearArgs {
     const int32_t* rows_dev;
     int rows_cap, N, K, act;
     int n_tiles;                                 // N / (32 NJ)
-    int panel;                                   // feature tiles of a panel, see tile_of()
+    int panel;                                   // feature tiles of a panel, see LinearWalk
     uint32_t panel_magic, last_magic;            // div_magic() of panel and of the last panel's width
 };
 
@@ -118,12 +118,6 @@ constexpr int spread_at(int s, int slots, int count) {
     return -1;
 }
 
-// Number of LDS stages: as many as fit, up to eight.
-constexpr int linear_stages(int NJ, int MT) {
-    const int fit = kLdsBytes / (32 * (NJ + MT) * kTK * 2);
-    return fit < 8 ? fit : 8;
-}
-
 template <typename In, int NJ, int MT>
 __global__ __launch_bounds__(kWaveSize * kLinWaves, 1)
 void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uint16_t* x, const uint16_t* w, int K_, int panel,
@@ -133,28 +127,21 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
     // would not), which saves a few hundred rows 0.1 to 0.3 us a launch (817 x 768 x 3072 13.4 -> 13.1, 1334 x 768 x 768
     // 6.4 -> 6.2) and large launches nothing.
     const LinearArgs p{x, w, bias, res, y, rows_ptr, rows_cap, N_, K_, act, n_tiles, panel, panel_magic, last_magic};
-    constexpr int TN = 32 * NJ, TM = 32 * MT;                  // features x tokens of a tile, 2 x 2 wavefronts
+    typedef LinearShape<NJ, MT> Shape;
+    constexpr int TN = Shape::TN, TM = Shape::TM;              // features x tokens of a tile, 2 x 2 wavefronts
     constexpr int kXBytes = TM * kTK * 2, kWBytes = TN * kTK * 2;
     constexpr int kStageBytes = kXBytes + kWBytes;
-    constexpr int STAGES = linear_stages(NJ, MT);
-    static_assert(STAGES >= 2, "two stages must fit");
-    constexpr bool TWO = STAGES == 2;
-    constexpr bool RELAX = STAGES >= 4;
-    constexpr int kAheadX = TWO ? 2 : (RELAX ? STAGES - 1 : STAGES);   // step whose x loads go with half B (TWO: A) of step 0
-    constexpr int kAheadW = TWO ? 2 : kAheadX - 1;                     // ... w loads with half A (TWO: B)
+    constexpr int STAGES = Shape::kStages;
+    constexpr bool TWO = Shape::kTwo, RELAX = Shape::kRelax;
+    constexpr int kAheadX = Shape::kAheadX, kAheadW = Shape::kAheadW;
     __shared__ __attribute__((aligned(1024))) uint4 stage_lds[STAGES * kStageBytes / 16];
 
     const int N = p.N;
     int rows = p.rows_cap;
     if (p.rows_dev) { const int r = *p.rows_dev; rows = r < rows ? r : rows; }
     rows = __builtin_amdgcn_readfirstlane(rows);
-    const int m_tiles = (rows + TM - 1) / TM;
-    const int total = m_tiles * p.n_tiles;
-    const int xcd = blockIdx.x % kXcds;
-    const int per_xcd = (total + kXcds - 1) / kXcds;
-    const int t_end = per_xcd * (xcd + 1) < total ? per_xcd * (xcd + 1) : total;
-    const int stride = gridDim.x / kXcds;
-    const int t_first = per_xcd * xcd + blockIdx.x / kXcds;
+    const LinearWalk walk(rows, TM, p.n_tiles, p.panel, p.panel_magic, p.last_magic, blockIdx.x, gridDim.x);
+    const int t_first = walk.t_first, t_end = walk.t_end, stride = walk.stride;
     if (t_first >= t_end) return;
 
     const int tid = threadIdx.x;
@@ -163,21 +150,6 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
     const int col = lane & 15;
     const int g = lane >> 4;
     const int wn = wave & 1, wm = wave >> 1;
-
-    // tile number -> first row, first feature.  Panels of `panel` feature tiles, one after the other; inside a panel the
-    // feature tiles of a token tile come together.
-    auto tile_of = [&](int t, int& m0, int& n0) ALWAYS_INLINE {
-        int first = 0, width = p.panel;
-        while (t >= m_tiles * width) {                         // a few panels at most
-            t -= m_tiles * width;
-            first += width;
-            width = p.n_tiles - first < p.panel ? p.n_tiles - first : p.panel;
-        }
-        uint32_t mq, nr;
-        divmod((uint32_t)t, (uint32_t)width, width == p.panel ? p.panel_magic : p.last_magic, mq, nr);
-        m0 = (int)mq * TM;
-        n0 = (first + (int)nr) * TN;
-    };
 
     // ---- loads.  Instruction d of this wavefront covers rows 8*(count*wave + d) + lane/8 of its operand tile; the
     // lane's LDS slot is position lane%8 of that row = chunk (lane%8) ^ ((row>>1)&3).
@@ -193,11 +165,11 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
     for (int i = 0; i < kWI; ++i) voff_w[i] = (uint32_t)(8 * (kWI * wave + i) + (lane >> 3)) * row_bytes + chunk;
     const uint32_t x_dst = kXI * 1024 * wave, w_dst = kXBytes + kWI * 1024 * wave;
 
-    // Two cursors walk (tile, step) ahead of the arithmetic.  Past the last tile the range is empty: such loads touch no
-    // memory.  Rows past the end of x are out of range too and arrive as zeros (their results are not stored).
+    // Two cursors walk (tile, step) ahead of the arithmetic.  Rows past the end of x and everything past the last tile are
+    // out of range: such loads touch no memory (see LinearCursor) and arrive as zeros (their results are not stored).
     u32x4 x_rsrc, w_rsrc;
-    uint32_t x_soff = 0, w_soff = 0;
-    int x_tile = t_first, w_tile = t_first;
+    LinearCursor x_cur, w_cur;
+    x_cur.tile = w_cur.tile = t_first;
     auto set_rsrc = [&](u32x4& r, const uint16_t* base, uint32_t bytes) ALWAYS_INLINE {
         const uint64_t a = reinterpret_cast<uint64_t>(base);
         r[0] = __builtin_amdgcn_readfirstlane((uint32_t)a);
@@ -205,27 +177,10 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
         r[2] = __builtin_amdgcn_readfirstlane(bytes);
         r[3] = 0x00020000u;
     };
-    auto set_x = [&]() ALWAYS_INLINE {
-        int m0, n0;
-        tile_of(x_tile < t_end ? x_tile : t_first, m0, n0);
-        const int live = rows - m0 < TM ? rows - m0 : TM;
-        set_rsrc(x_rsrc, p.x + (int64_t)m0 * p.K, x_tile < t_end ? (uint32_t)live * row_bytes : 0u);
-        x_soff = 0;
-    };
-    auto set_w = [&]() ALWAYS_INLINE {
-        int m0, n0;
-        tile_of(w_tile < t_end ? w_tile : t_first, m0, n0);
-        set_rsrc(w_rsrc, p.w + (int64_t)n0 * p.K, w_tile < t_end ? (uint32_t)TN * row_bytes : 0u);
-        w_soff = 0;
-    };
-    auto next_x = [&]() ALWAYS_INLINE {
-        x_soff += kTK * 2;
-        if (x_soff == row_bytes) { x_tile += stride; set_x(); }
-    };
-    auto next_w = [&]() ALWAYS_INLINE {
-        w_soff += kTK * 2;
-        if (w_soff == row_bytes) { w_tile += stride; set_w(); }
-    };
+    auto set_x = [&]() ALWAYS_INLINE { set_rsrc(x_rsrc, p.x + (int64_t)x_cur.first * p.K, x_cur.bytes); };
+    auto set_w = [&]() ALWAYS_INLINE { set_rsrc(w_rsrc, p.w + (int64_t)w_cur.first * p.K, w_cur.bytes); };
+    auto next_x = [&]() ALWAYS_INLINE { if (x_cur.next<TM, TN, true>(walk, row_bytes)) set_x(); };
+    auto next_w = [&]() ALWAYS_INLINE { if (w_cur.next<TM, TN, false>(walk, row_bytes)) set_w(); };
 
     // ---- LDS addresses of this lane's operands: x (B operand) row 16 mt + col, w (A operand) of feature tile j: row
     // 32 (j/2) + 8 (col/4) + 4 (j%2) + col%4; chunk 2g + half
@@ -278,8 +233,8 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
             const int d = spread_at(q, kLeft, kLoads);
             __builtin_amdgcn_sched_barrier(0);
             if (d < 0) mma_acc<FIRST>(In{}, a0[m / MT], b0[snake(m, MT)], acc[m / MT][snake(m, MT)]);
-            else if (TWO) mma_acc_dma<FIRST>(In{}, a0[m / MT], b0[snake(m, MT)], acc[m / MT][snake(m, MT)], fill + x_dst, d * 1024, voff_x[d < kXI ? d : 0], x_rsrc, x_soff);
-            else mma_acc_dma<FIRST>(In{}, a0[m / MT], b0[snake(m, MT)], acc[m / MT][snake(m, MT)], fill + w_dst, d * 1024, voff_w[d < kWI ? d : 0], w_rsrc, w_soff);
+            else if (TWO) mma_acc_dma<FIRST>(In{}, a0[m / MT], b0[snake(m, MT)], acc[m / MT][snake(m, MT)], fill + x_dst, d * 1024, voff_x[d < kXI ? d : 0], x_rsrc, x_cur.soff);
+            else mma_acc_dma<FIRST>(In{}, a0[m / MT], b0[snake(m, MT)], acc[m / MT][snake(m, MT)], fill + w_dst, d * 1024, voff_w[d < kWI ? d : 0], w_rsrc, w_cur.soff);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (TWO) next_x();
@@ -303,8 +258,8 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
             const int d = spread_at(m, NS, TWO ? kWI : kXI);
             __builtin_amdgcn_sched_barrier(0);
             if (d < 0) mma_acc<false>(In{}, a1[snake(m, NJ)], b1[m / NJ], acc[snake(m, NJ)][m / NJ]);
-            else if (TWO) mma_acc_dma<false>(In{}, a1[snake(m, NJ)], b1[m / NJ], acc[snake(m, NJ)][m / NJ], fill + w_dst, d * 1024, voff_w[d < kWI ? d : 0], w_rsrc, w_soff);
-            else mma_acc_dma<false>(In{}, a1[snake(m, NJ)], b1[m / NJ], acc[snake(m, NJ)][m / NJ], fill + x_dst, d * 1024, voff_x[d < kXI ? d : 0], x_rsrc, x_soff);
+            else if (TWO) mma_acc_dma<false>(In{}, a1[snake(m, NJ)], b1[m / NJ], acc[snake(m, NJ)][m / NJ], fill + w_dst, d * 1024, voff_w[d < kWI ? d : 0], w_rsrc, w_cur.soff);
+            else mma_acc_dma<false>(In{}, a1[snake(m, NJ)], b1[m / NJ], acc[snake(m, NJ)][m / NJ], fill + x_dst, d * 1024, voff_x[d < kXI ? d : 0], x_rsrc, x_cur.soff);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (TWO) {
@@ -323,24 +278,26 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
         for (int jp = 0; jp < NJ / 2; ++jp)
             bias_raw[jp] = p.bias ? *reinterpret_cast<const uint4*>(p.bias + n0 + wn * 16 * NJ + 32 * jp + 8 * g) : make_uint4(0, 0, 0, 0);
     };
+    x_cur.set<TM, TN, true>(walk, row_bytes);
     set_x();
+    w_cur.set<TM, TN, false>(walk, row_bytes);
     set_w();
     {
         constexpr int kFillX = TWO ? 2 : kAheadX, kFillW = TWO ? 2 : kAheadW;
 #pragma unroll
         for (int st = 0; st < kFillX; ++st) {
 #pragma unroll
-            for (int d = 0; d < kXI; ++d) buf_dma16(lds0 + st * kStageBytes + x_dst + d * 1024, voff_x[d], x_rsrc, x_soff);
+            for (int d = 0; d < kXI; ++d) buf_dma16(lds0 + st * kStageBytes + x_dst + d * 1024, voff_x[d], x_rsrc, x_cur.soff);
             next_x();
             if (st < kFillW) {
 #pragma unroll
-                for (int d = 0; d < kWI; ++d) buf_dma16(lds0 + st * kStageBytes + w_dst + d * 1024, voff_w[d], w_rsrc, w_soff);
+                for (int d = 0; d < kWI; ++d) buf_dma16(lds0 + st * kStageBytes + w_dst + d * 1024, voff_w[d], w_rsrc, w_cur.soff);
                 next_w();
             }
         }
         wait_vm<(kFillX - 1) * kXI + (kFillW - 1) * kWI>();    // step 0 has landed
     }
-    tile_of(t_first, m0, n0);
+    walk.tile_of(t_first, TM, TN, m0, n0);
     load_bias();
     __syncthreads();
 #pragma unroll
@@ -389,7 +346,7 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
 #pragma unroll
         for (int jp = 0; jp < NJ / 2; ++jp) unpack8(In{}, bias_raw[jp], bias8[jp]);
         if (t + stride < t_end) {
-            tile_of(t + stride, m0, n0);
+            walk.tile_of(t + stride, TM, TN, m0, n0);
             load_bias();                                       // the next tile's
         }
         auto offset = [&](int mt) ALWAYS_INLINE -> int64_t {
@@ -444,9 +401,6 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
         landed = true;
     }
 }
-
-// The tile shapes there are, as {NJ, MT}: 32 NJ features x 32 MT tokens.
-#define LINEAR_SHAPES(X) X(8, 8) X(8, 7) X(8, 6) X(8, 5) X(8, 4) X(6, 4) X(6, 3) X(6, 2) X(4, 4) X(4, 3) X(4, 2) X(2, 4) X(2, 2) X(2, 1)
 
 template <typename In>
 hipError_t launch_linear_tile(int nj, int mt, int groups, const LinearArgs& args, hipStream_t stream) {

@@ -1,0 +1,150 @@
+// Which tile shape a linear layer takes, the order in which linear_kernel goes through its tiles, and what its loads may touch
+// (internal; no HIP in here, so that CPU tests compile this very code and follow every load of a call against the ends of its
+// buffers).
+#pragma once
+
+#include <stdint.h>
+
+#if defined(__HIP__) || defined(__HIPCC__)
+#define RAGGED_HD __host__ __device__ __attribute__((always_inline))
+#else
+#define RAGGED_HD
+#endif
+
+namespace ragged {
+
+constexpr int kTK = 64;                          // contraction elements per step: 128-byte LDS rows
+constexpr int kLdsBytes = 160 * 1024;
+constexpr int kLinearXcds = 8;
+
+// Number of LDS stages: as many as fit, up to eight.
+constexpr int linear_stages(int NJ, int MT) {
+    const int fit = kLdsBytes / (32 * (NJ + MT) * kTK * 2);
+    return fit < 8 ? fit : 8;
+}
+
+// Constants of a tile shape: 32 NJ features x 32 MT tokens.
+template <int NJ, int MT>
+struct LinearShape {
+    static constexpr int TN = 32 * NJ, TM = 32 * MT;           // features x tokens of a tile
+    static constexpr int kStages = linear_stages(NJ, MT);
+    static_assert(kStages >= 2, "two stages must fit");
+    static constexpr bool kTwo = kStages == 2;
+    static constexpr bool kRelax = kStages >= 4;
+    static constexpr int kAheadX = kTwo ? 2 : (kRelax ? kStages - 1 : kStages);   // step whose x loads go with half B (two stages: A) of step 0
+    static constexpr int kAheadW = kTwo ? 2 : kAheadX - 1;                        // ... w loads with half A (two stages: B)
+};
+
+// The tiles of one work-group of a call: t_first, t_first + stride, ... < t_end.
+struct LinearWalk {
+    int rows, m_tiles, n_tiles, panel;                         // panel: feature tiles of a panel
+    uint32_t panel_magic, last_magic;                          // div_magic() of panel and of the last panel's width
+    int t_first, t_end, stride;
+
+    RAGGED_HD LinearWalk(int rows_, int TM, int n_tiles_, int panel_, uint32_t panel_magic_, uint32_t last_magic_, int block, int grid)
+        : rows(rows_), m_tiles((rows_ + TM - 1) / TM), n_tiles(n_tiles_), panel(panel_), panel_magic(panel_magic_), last_magic(last_magic_) {
+        const int total = m_tiles * n_tiles;
+        const int xcd = block % kLinearXcds;
+        const int per_xcd = (total + kLinearXcds - 1) / kLinearXcds;
+        t_end = per_xcd * (xcd + 1) < total ? per_xcd * (xcd + 1) : total;
+        stride = grid / kLinearXcds;
+        t_first = per_xcd * xcd + block / kLinearXcds;
+    }
+
+    // tile number -> first row, first feature.  Panels of `panel` feature tiles, one after the other; inside a panel the
+    // feature tiles of a token tile come together.
+    RAGGED_HD void tile_of(int t, int TM, int TN, int& m0, int& n0) const {
+        int first = 0, width = panel;
+        while (t >= m_tiles * width) {                         // a few panels at most
+            t -= m_tiles * width;
+            first += width;
+            width = n_tiles - first < panel ? n_tiles - first : panel;
+        }
+        // t / width, as divmod() does it
+        uint32_t mq = (uint32_t)(((uint64_t)(uint32_t)t * (width == panel ? panel_magic : last_magic)) >> 32);
+        uint32_t nr = (uint32_t)t - mq * (uint32_t)width;
+        if (nr >= (uint32_t)width) { ++mq; nr -= (uint32_t)width; }
+        m0 = (int)mq * TM;
+        n0 = (first + (int)nr) * TN;
+    }
+};
+
+// One operand's place in (tile, step), ahead of the arithmetic: the loads of a step read
+//     base + first * K elements + soff + [0, bytes - soff)
+// and everything further arrives as zeros.  Past the last tile the range is empty, and there the offset stays 0: the range
+// check is offset >= bytes - soff in some descriptions of the hardware and offset >= bytes in others, and with bytes == 0
+// the two agree only for soff == 0.
+struct LinearCursor {
+    int tile;
+    int first;                                                 // first row (x) or feature (w) of the tile
+    uint32_t bytes, soff, step;                                // step: what soff advances by
+
+    template <int TM, int TN, bool X>
+    RAGGED_HD void set(const LinearWalk& walk, uint32_t row_bytes) {
+        const bool inside = tile < walk.t_end;
+        int m0, n0;
+        walk.tile_of(inside ? tile : walk.t_first, TM, TN, m0, n0);
+        const int live = X ? (walk.rows - m0 < TM ? walk.rows - m0 : TM) : TN;
+        first = X ? m0 : n0;
+        bytes = inside ? (uint32_t)live * row_bytes : 0u;
+        step = inside ? kTK * 2u : 0u;
+        soff = 0;
+    }
+    // true: the tile is done, the next one has to be set
+    template <int TM, int TN, bool X>
+    RAGGED_HD bool next(const LinearWalk& walk, uint32_t row_bytes) {
+        soff += step;
+        if (soff != row_bytes) return false;
+        tile += walk.stride;
+        set<TM, TN, X>(walk, row_bytes);
+        return true;
+    }
+};
+
+// The tile shapes there are, as {NJ, MT}: 32 NJ features x 32 MT tokens.
+#define LINEAR_SHAPES(X) X(8, 8) X(8, 7) X(8, 6) X(8, 5) X(8, 4) X(6, 4) X(6, 3) X(6, 2) X(4, 4) X(4, 3) X(4, 2) X(2, 4) X(2, 2) X(2, 1)
+
+// Tile shape.  The kernel runs one work-group per CU and hands the tiles out evenly, so a call takes
+//     ceil(tiles / 256) * (k-steps * step_ns + tile_ns [+ GELU]),
+// and the shape with the least of it is taken (rows: the caller's estimate, or the capacity).  step_ns is what a step of
+// 64 k costs a CU (arithmetic and LDS traffic of the tile plus one barrier), tile_ns what a tile costs besides (epilogue,
+// first operands): both fitted to single-round launches at 768-wide layers, K = 768 and 3072, fp16.  Large tiles need
+// the fewest operand bytes per product, small ones fill the chip when rows are few, and the heights in between are there
+// because a round is paid whole: 12 544 x 768 x 3072 takes 52 us in 237 tiles of 160 rows, 61 in 147 of 256 rows; 1334 x
+// 2304 x 768 takes 8.9 in 252 tiles of 96 x 128, 11.9 in 378 of 64 x 128, 15 in 81 of 160 x 256; 200 x 768 x 3072 takes 11.4 in
+// 84 tiles of 32 x 64, 12.8 in 48 of 64 x 64 (a CU draws its operands at about 87 GB/s, so fewer bytes per CU is less time).
+constexpr int kCus = 256;
+constexpr int kGeluNs = 80;                                    // per nj * mt
+struct TileShape { int nj, mt, step_ns, tile_ns; };
+constexpr TileShape kTileShapes[] = {
+    {8, 8, 1040, 6000}, {8, 7, 900, 5800}, {8, 6, 800, 5300}, {8, 5, 670, 4700}, {8, 4, 580, 3300},
+    {6, 4, 475, 2600}, {6, 3, 410, 1700}, {6, 2, 385, 1000}, {4, 4, 375, 1600}, {4, 3, 340, 1100},
+    {4, 2, 300, 600}, {2, 4, 290, 800}, {2, 2, 235, 600}, {2, 1, 180, 500}};
+// rows: the caller's estimate, or the capacity
+inline TileShape pick_linear_shape(int rows, int N, int K, int act) {
+    TileShape pick{2, 2, 0, 0};                                // N is a multiple of 64: this one always fits
+    int64_t best = INT64_MAX;
+    for (const TileShape& c : kTileShapes) {
+        if (N % (32 * c.nj) != 0) continue;
+        const int64_t tiles = (int64_t)((rows + 32 * c.mt - 1) / (32 * c.mt)) * (N / (32 * c.nj));
+        const int64_t cost = (tiles + kCus - 1) / kCus * (K / kTK * c.step_ns + c.tile_ns + (act == 1 ? kGeluNs * c.nj * c.mt : 0));
+        if (cost < best) { best = cost; pick = c; }
+    }
+    return pick;
+}
+// Feature tiles per panel: the 32 CUs of an XCD then work on a patch of about 6 x 5 tiles, which pulls fewest operand
+// bytes into its L2 (12 544 x 3072 x 768: 78 -> 72.5 us against whole rows of tiles; widths of 4 to 6 are alike).
+constexpr int kPanel = 6;
+struct LinearGrid {
+    int n_tiles, panel, last, groups;                          // last: width of the last panel
+    LinearGrid(int nj, int mt, int rows_cap, int N) {
+        n_tiles = N / (32 * nj);
+        const int panels = (n_tiles + kPanel - 1) / kPanel;
+        panel = (n_tiles + panels - 1) / panels;
+        last = n_tiles - (n_tiles - 1) / panel * panel;
+        const int64_t tiles = (int64_t)((rows_cap + 32 * mt - 1) / (32 * mt)) * n_tiles;
+        groups = (int)(tiles < kCus ? (tiles + kLinearXcds - 1) / kLinearXcds * kLinearXcds : kCus);
+    }
+};
+
+}  // namespace ragged

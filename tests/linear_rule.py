@@ -1,0 +1,40 @@
+"""The library's own tile rule and tile walk of the linear layers (csrc/linear_walk.h), compiled for the CPU."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+from paper_2604_15408_amd.build import CSRC
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@functools.lru_cache(None)
+def lib() -> ctypes.CDLL:
+    with tempfile.TemporaryDirectory() as d:
+        so = os.path.join(d, "linear_walk_check.so")
+        subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-Wextra", "-Werror",
+                        f"-I{CSRC}", "-o", so, os.path.join(HERE, "linear_walk_check.cpp")], check=True)
+        return ctypes.CDLL(so)
+
+
+# tiles of 32 nj features x 32 mt rows
+SHAPES = [(8, 8), (8, 7), (8, 6), (8, 5), (8, 4), (6, 4), (6, 3), (6, 2), (4, 4), (4, 3), (4, 2), (2, 4), (2, 2), (2, 1)]
+
+
+def shapes():
+    """[(nj, mt, LDS stages)] as the library has them."""
+    out = (ctypes.c_int * 3)()
+    res = []
+    for i in range(lib().linear_shape_count()):
+        lib().linear_shape(i, out)
+        res.append(tuple(out))
+    return res
+
+
+def pick(rows_hint, rows, N, K, act):
+    """(nj, mt, tiles) of a call over `rows` rows with this row estimate."""
+    out = (ctypes.c_int * 3)()
+    lib().linear_pick(rows_hint, rows, N, K, {"none": 0, "gelu": 1}[act], out)
+    return tuple(out)
