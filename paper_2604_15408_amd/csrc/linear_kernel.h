@@ -137,11 +137,10 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
     __shared__ __attribute__((aligned(1024))) uint4 stage_lds[STAGES * kStageBytes / 16];
 
     const int N = p.N;
-    int rows = p.rows_cap;
-    if (p.rows_dev) { const int r = *p.rows_dev; rows = r < rows ? r : rows; }
-    rows = __builtin_amdgcn_readfirstlane(rows);
-    const LinearWalk walk(rows, TM, p.n_tiles, p.panel, p.panel_magic, p.last_magic, blockIdx.x, gridDim.x);
-    const int t_first = walk.t_first, t_end = walk.t_end, stride = walk.stride;
+    int given = p.rows_cap;
+    if (p.rows_dev) { const int r = *p.rows_dev; given = r < given ? r : given; }
+    const LinearWalk walk(__builtin_amdgcn_readfirstlane(given), TM, p.n_tiles, p.panel, p.panel_magic, p.last_magic, blockIdx.x, gridDim.x);
+    const int rows = walk.rows, t_first = walk.t_first, t_end = walk.t_end, stride = walk.stride;
     if (t_first >= t_end) return;
 
     const int tid = threadIdx.x;

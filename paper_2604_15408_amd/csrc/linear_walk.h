@@ -37,12 +37,12 @@ struct LinearShape {
 
 // The tiles of one work-group of a call: t_first, t_first + stride, ... < t_end.
 struct LinearWalk {
-    int rows, m_tiles, n_tiles, panel;                         // panel: feature tiles of a panel
+    int rows, m_tiles, n_tiles, panel;                         // rows: 0 where the device's count is negative; panel: feature tiles of a panel
     uint32_t panel_magic, last_magic;                          // div_magic() of panel and of the last panel's width
     int t_first, t_end, stride;
 
     RAGGED_HD LinearWalk(int rows_, int TM, int n_tiles_, int panel_, uint32_t panel_magic_, uint32_t last_magic_, int block, int grid)
-        : rows(rows_), m_tiles((rows_ + TM - 1) / TM), n_tiles(n_tiles_), panel(panel_), panel_magic(panel_magic_), last_magic(last_magic_) {
+        : rows(rows_ > 0 ? rows_ : 0), m_tiles((rows + TM - 1) / TM), n_tiles(n_tiles_), panel(panel_), panel_magic(panel_magic_), last_magic(last_magic_) {
         const int total = m_tiles * n_tiles;
         const int xcd = block % kLinearXcds;
         const int per_xcd = (total + kLinearXcds - 1) / kLinearXcds;

@@ -35,7 +35,7 @@ def check_linear(M, N, K, dtype="f16", act="none", bias=True, residual=False, ro
     binding.ragged_linear(x.to(DEV), w.to(DEV), None if b is None else b.to(DEV), None if r is None else r.to(DEV),
                           y, rows_dev, act, rows_hint=hint)
     torch.cuda.synchronize()
-    live = cap if rows is None else min(rows, cap)
+    live = cap if rows is None else max(0, min(rows, cap))
     got = y.cpu()
     assert torch.all(got[live:] == 77.0), "rows past the device row count were written"
     if live == 0:
@@ -72,6 +72,9 @@ def test_linear_device_row_count():
     check_linear(640, 256, 128, rows=128)
     check_linear(640, 256, 128, rows=513)
     check_linear(640, 256, 128, rows=5000)                      # larger than the capacity: the capacity wins
+    for rows in (-1, -(1 << 30), -(1 << 31)):                   # negative: no rows, also where rows * N would wrap
+        check_linear(64, 4096, 64, rows=rows)
+        check_linear(300, 3072, 128, "bf16", "gelu", residual=True, rows=rows)
 
 
 @pytest.mark.parametrize("dtype,act,residual", [("f16", "none", False), ("bf16", "gelu", True)])

@@ -29,3 +29,11 @@ def test_every_load_stays_inside_its_operand(nj, mt):
         follow(nj, mt, tm + 3, tn * 2, K, cap=50 * tm)          # far fewer rows than the capacity
     follow(nj, mt, 2 * tm + 1, tn, 1 << 22)                     # the widest rows there are
     follow(nj, mt, 0, tn * 3, 768, cap=tm)
+
+
+@pytest.mark.parametrize("nj,mt", rule.SHAPES)
+def test_a_negative_device_row_count_is_no_work(nj, mt):
+    """The number of tiles of such a count must not wrap round to a positive one."""
+    for rows in (-1, -32 * mt, -32 * mt - 1, -(1 << 30), -(1 << 31) + 1, -(1 << 31)):
+        for n_tiles in (1, 24, 33, 48, 63, 64, 96, 128, 512):
+            follow(nj, mt, rows, 32 * nj * n_tiles, 64, cap=300)
