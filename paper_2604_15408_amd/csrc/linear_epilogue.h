@@ -21,7 +21,7 @@ __device__ __forceinline__ float gelu_erf(float t) {
     p = __builtin_fmaf(p, a, -0.45876961946487427f);
     p = __builtin_fmaf(p, a, -1.1512017250061035f);
     p = __builtin_fmaf(p, a, -0.9999932646751404f);
-    return __builtin_fmaf(-a, __builtin_amdgcn_exp2f(p), fmaxf(t, 0.f));
+    return __builtin_fmaf(-a, __builtin_amdgcn_exp2f(p), __builtin_elementwise_maximum(t, 0.f));   // (keeps a NaN, as fmaxf does not)
 }
 
 __device__ __forceinline__ void unpack16(F16, const uint4& a, const uint4& b, float (&v)[16]) {

@@ -38,3 +38,18 @@ def pick(rows_hint, rows, N, K, act):
     out = (ctypes.c_int * 3)()
     lib().linear_pick(rows_hint, rows, N, K, {"none": 0, "gelu": 1}[act], out)
     return tuple(out)
+
+
+@functools.lru_cache(None)
+def call_for(nj, mt, act, K):
+    """(rows_hint, N) with the fewest outputs for which the rule picks this shape."""
+    best = None
+    for n_tiles in range(1, 65):
+        N = 32 * nj * n_tiles
+        if N > 8192:
+            break
+        for m_tiles in range(1, 513):
+            for hint in (32 * mt * m_tiles - 31, 32 * mt * m_tiles):
+                if (best is None or hint * N < best[0] * best[1]) and hint * N <= 1 << 25 and pick(hint, hint, N, K, act)[:2] == (nj, mt):
+                    best = (hint, N)
+    return best

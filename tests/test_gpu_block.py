@@ -11,6 +11,7 @@ import torch
 import oracle
 from paper_2604_15408_amd import binding
 from paper_2604_15408_amd import workloads as wl
+from tests import linear_rule as rule
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -177,6 +178,46 @@ def test_linear_residual_in_place_and_gelu_tails():
     want = oracle.linear(wl.to_words(t), wl.to_words(eye), act="gelu")
     err = np.abs(out.cpu().to(torch.float64).numpy() - want)
     assert np.all(err <= 2.0 ** -10 * np.abs(want) + 1.2e-7), float(err.max())     # fp16 subnormal spacing 6e-8
+
+
+@pytest.mark.parametrize("residual", [False, True])
+@pytest.mark.parametrize("nj,mt", rule.SHAPES)
+def test_gelu_keeps_nan_and_infinities(nj, mt, residual):
+    """GELU(NaN) = NaN, GELU(inf) = inf and GELU(-inf) = 0 (the limit) in every tile shape, from a bias and from an input row;
+    everything beside them is as without them."""
+    stages = {s[:2]: s[2] for s in rule.shapes()}[nj, mt]
+    K = 64 * (stages + 2)
+    hint, N = rule.call_for(nj, mt, "gelu", K)
+    dtype = ("f16", "bf16")[(nj + mt + residual) % 2]
+    tdt = _TD[dtype]
+    rows = 32 * mt + 1
+    cap = max(rows, hint)
+    x, w, b = _rand((rows, K), 1, tdt), _rand((N, K), 2, tdt, K ** -0.5), _rand((N,), 3, tdt, 0.5)
+    r = _rand((rows, N), 4, tdt)
+    n = torch.arange(N)
+    b[n % 16 == 3], b[n % 16 == 5], b[n % 16 == 9] = float("nan"), float("inf"), float("-inf")
+    x[1, K - 1] = float("nan")
+    x[rows - 1, 2] = float("inf")
+    x_gpu = torch.zeros(cap, K, dtype=tdt, device=DEV)
+    x_gpu[:rows] = x.to(DEV)
+    y = torch.zeros(cap, N, dtype=tdt, device=DEV)
+    if residual:
+        y[:rows] = r.to(DEV)
+    binding.ragged_linear(x_gpu, w.to(DEV), b.to(DEV), y if residual else None, y,
+                          torch.tensor([rows], dtype=torch.int32, device=DEV), "gelu", rows_hint=hint)
+    torch.cuda.synchronize()
+    got = y[:rows].cpu().to(torch.float64)
+    z = x.double() @ w.double().T + b.double()
+    want = torch.where(torch.isneginf(z), 0.0, 0.5 * z * torch.special.erfc(-z * 0.5 ** 0.5))
+    if residual:
+        want = want + r.double()
+    assert torch.equal(torch.isnan(got), torch.isnan(want))
+    assert torch.equal(torch.isposinf(got), torch.isposinf(want)) and not torch.isneginf(got).any()
+    fin = torch.isfinite(want)
+    assert torch.isneginf(z[fin]).any() and fin.float().mean() > 0.5
+    S = torch.nan_to_num(x.double().abs(), nan=0.0, posinf=0.0) @ w.double().abs().T
+    bound = _ULP[dtype] * want.abs() + 2.0 ** -15 * S + 1e-6
+    assert torch.all((got - want).abs()[fin] <= bound[fin])
 
 
 @pytest.mark.parametrize("M,C,dtype", [(1, 8, "f16"), (5, 768, "f16"), (1334, 768, "f16"), (33, 192, "bf16"),
