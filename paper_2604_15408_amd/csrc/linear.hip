@@ -116,12 +116,12 @@ hipError_t launch_linear(const void* x, const void* w, const void* bias, const v
                          const int32_t* rows_dev, int rows_hint, int N, int K, int act, ragged_dtype dt,
                          hipStream_t stream) {
     const TileShape c = pick_linear_shape(rows_hint, N, K, act);
-    const LinearGrid g(c.nj, c.mt, rows_cap, N);
+    const LinearGrid g(c.nj, c.mt, c.per_cu, rows_cap, N);
     const LinearArgs args{static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w), static_cast<const uint16_t*>(bias),
                           static_cast<const uint16_t*>(res), static_cast<uint16_t*>(y), rows_dev, rows_cap, N, K, act, g.n_tiles,
                           g.panel, div_magic((uint32_t)g.panel), div_magic((uint32_t)g.last)};
-    return dt == RAGGED_F16 ? launch_linear_f16(c.nj, c.mt, g.groups, args, stream)
-                            : launch_linear_bf16(c.nj, c.mt, g.groups, args, stream);
+    return dt == RAGGED_F16 ? launch_linear_f16(c, g.groups, args, stream)
+                            : launch_linear_bf16(c, g.groups, args, stream);
 }
 
 int layernorm_max_width() { return kWaveSize * kLnChunks * 8; }

@@ -3,8 +3,8 @@
 
 namespace ragged {
 
-hipError_t launch_linear_bf16(int nj, int mt, int groups, const LinearArgs& args, hipStream_t stream) {
-    return launch_linear_tile<BF16>(nj, mt, groups, args, stream);
+hipError_t launch_linear_bf16(const TileShape& shape, int groups, const LinearArgs& args, hipStream_t stream) {
+    return launch_linear_tile<BF16>(shape, groups, args, stream);
 }
 
 }  // namespace ragged

@@ -3,8 +3,8 @@
 
 namespace ragged {
 
-hipError_t launch_linear_f16(int nj, int mt, int groups, const LinearArgs& args, hipStream_t stream) {
-    return launch_linear_tile<F16>(nj, mt, groups, args, stream);
+hipError_t launch_linear_f16(const TileShape& shape, int groups, const LinearArgs& args, hipStream_t stream) {
+    return launch_linear_tile<F16>(shape, groups, args, stream);
 }
 
 }  // namespace ragged

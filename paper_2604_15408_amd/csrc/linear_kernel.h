@@ -118,8 +118,8 @@ constexpr int spread_at(int s, int slots, int count) {
     return -1;
 }
 
-template <typename In, int NJ, int MT>
-__global__ __launch_bounds__(kWaveSize * kLinWaves, 1)
+template <typename In, int NJ, int MT, int PER_CU>
+__global__ __launch_bounds__(kWaveSize * kLinWaves, PER_CU)
 void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uint16_t* x, const uint16_t* w, int K_, int panel,
                    uint32_t panel_magic, uint32_t last_magic, const uint16_t* bias, const uint16_t* res, uint16_t* y, int N_,
                    int act) {
@@ -127,7 +127,7 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
     // would not), which saves a few hundred rows 0.1 to 0.3 us a launch (817 x 768 x 3072 13.4 -> 13.1, 1334 x 768 x 768
     // 6.4 -> 6.2) and large launches nothing.
     const LinearArgs p{x, w, bias, res, y, rows_ptr, rows_cap, N_, K_, act, n_tiles, panel, panel_magic, last_magic};
-    typedef LinearShape<NJ, MT> Shape;
+    typedef LinearShape<NJ, MT, PER_CU> Shape;
     constexpr int TN = Shape::TN, TM = Shape::TM;              // features x tokens of a tile, 2 x 2 wavefronts
     constexpr int kXBytes = TM * kTK * 2, kWBytes = TN * kTK * 2;
     constexpr int kStageBytes = kXBytes + kWBytes;
@@ -200,6 +200,7 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
     auto read_b = [&](int h, int mt) ALWAYS_INLINE { return lds_vec(rb[h] + mt * 2048); };
 
     constexpr int NS = NJ * MT;                                // products of half a step = issue slots
+    static_assert(!TWO || NS >= 16, "the slots before the barrier of a half hold the address updates of two-stage rings");
     // ---- first half of a step: products of (a0, b0)
     auto half_a = [&](auto first_tag, uint32_t fill, uint32_t delta) ALWAYS_INLINE {
         constexpr bool FIRST = decltype(first_tag)::value;
@@ -402,16 +403,17 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
 }
 
 template <typename In>
-hipError_t launch_linear_tile(int nj, int mt, int groups, const LinearArgs& args, hipStream_t stream) {
-#define LINEAR_CASE(NJ, MT) \
-    if (nj == NJ && mt == MT) return launch_kernel(linear_kernel<In, NJ, MT>, dim3(groups), dim3(kWaveSize * kLinWaves), stream, args.rows_dev, args.rows_cap, \
-                             args.n_tiles, args.x, args.w, args.K, args.panel, args.panel_magic, args.last_magic, args.bias, args.res, \
-                             args.y, args.N, args.act);
+hipError_t launch_linear_tile(const TileShape& shape, int groups, const LinearArgs& args, hipStream_t stream) {
+#define LINEAR_CASE(NJ, MT, PER_CU) \
+    if (shape.nj == NJ && shape.mt == MT && shape.per_cu == PER_CU) \
+        return launch_kernel(linear_kernel<In, NJ, MT, PER_CU>, dim3(groups), dim3(kWaveSize * kLinWaves), stream, args.rows_dev, \
+                             args.rows_cap, args.n_tiles, args.x, args.w, args.K, args.panel, args.panel_magic, args.last_magic, \
+                             args.bias, args.res, args.y, args.N, args.act);
     LINEAR_SHAPES(LINEAR_CASE)
 #undef LINEAR_CASE
     return hipErrorInvalidValue;
 }
-hipError_t launch_linear_f16(int nj, int mt, int groups, const LinearArgs& args, hipStream_t stream);
-hipError_t launch_linear_bf16(int nj, int mt, int groups, const LinearArgs& args, hipStream_t stream);
+hipError_t launch_linear_f16(const TileShape& shape, int groups, const LinearArgs& args, hipStream_t stream);
+hipError_t launch_linear_bf16(const TileShape& shape, int groups, const LinearArgs& args, hipStream_t stream);
 
 }  // namespace ragged

@@ -18,16 +18,16 @@ constexpr int kLdsBytes = 160 * 1024;
 constexpr int kLinearXcds = 8;
 
 // Number of LDS stages: as many as fit, up to eight.
-constexpr int linear_stages(int NJ, int MT) {
-    const int fit = kLdsBytes / (32 * (NJ + MT) * kTK * 2);
+constexpr int linear_stages(int NJ, int MT, int PER_CU) {
+    const int fit = kLdsBytes / PER_CU / (32 * (NJ + MT) * kTK * 2);
     return fit < 8 ? fit : 8;
 }
 
-// Constants of a tile shape: 32 NJ features x 32 MT tokens.
-template <int NJ, int MT>
+// Constants of a tile shape: 32 NJ features x 32 MT tokens, PER_CU work-groups (1 or 2) on a CU.
+template <int NJ, int MT, int PER_CU>
 struct LinearShape {
     static constexpr int TN = 32 * NJ, TM = 32 * MT;           // features x tokens of a tile
-    static constexpr int kStages = linear_stages(NJ, MT);
+    static constexpr int kStages = linear_stages(NJ, MT, PER_CU);
     static_assert(kStages >= 2, "two stages must fit");
     static constexpr bool kTwo = kStages == 2;
     static constexpr bool kRelax = kStages >= 4;
@@ -101,33 +101,45 @@ struct LinearCursor {
     }
 };
 
-// The tile shapes there are, as {NJ, MT}: 32 NJ features x 32 MT tokens.
-#define LINEAR_SHAPES(X) X(8, 8) X(8, 7) X(8, 6) X(8, 5) X(8, 4) X(6, 4) X(6, 3) X(6, 2) X(4, 4) X(4, 3) X(4, 2) X(2, 4) X(2, 2) X(2, 1)
+// The tile shapes there are, as {NJ, MT, PER_CU}: 32 NJ features x 32 MT tokens, PER_CU work-groups on a CU.
+#define LINEAR_SHAPES(X) \
+    X(8, 8, 1) X(8, 7, 1) X(8, 6, 1) X(8, 5, 1) X(8, 4, 1) X(6, 4, 1) X(6, 2, 1) X(4, 4, 1) X(4, 3, 1) X(2, 1, 1) \
+    X(6, 3, 2) X(4, 4, 2) X(4, 2, 2) X(2, 4, 2) X(2, 2, 2)
 
-// Tile shape.  The kernel runs one work-group per CU and hands the tiles out evenly, so a call takes
-//     ceil(tiles / 256) * (k-steps * step_ns + tile_ns [+ GELU]),
-// and the shape with the least of it is taken (rows: the caller's estimate, or the capacity).  step_ns is what a step of
-// 64 k costs a CU (arithmetic and LDS traffic of the tile plus one barrier), tile_ns what a tile costs besides (epilogue,
-// first operands): both fitted to single-round launches at 768-wide layers, K = 768 and 3072, fp16.  Large tiles need
-// the fewest operand bytes per product, small ones fill the chip when rows are few, and the heights in between are there
-// because a round is paid whole: 12 544 x 768 x 3072 takes 52 us in 237 tiles of 160 rows, 61 in 147 of 256 rows; 1334 x
-// 2304 x 768 takes 8.9 in 252 tiles of 96 x 128, 11.9 in 378 of 64 x 128, 15 in 81 of 160 x 256; 200 x 768 x 3072 takes 11.4 in
-// 84 tiles of 32 x 64, 12.8 in 48 of 64 x 64 (a CU draws its operands at about 87 GB/s, so fewer bytes per CU is less time).
+// Tile shape.  The tiles are handed out evenly, n = ceil(tiles / 256) to a CU.  Where one work-group has a CU to itself they
+// follow each other,
+//     n * (k-steps * step_ns + tile_ns + GELU),
+// where two share it, two at a time run in less than twice that, because the epilogue of one overlaps the products of the other,
+//     n / 2 * (k-steps * pair_step_ns + pair_tile_ns + GELU) + n % 2 * (k-steps * step_ns + tile_ns + GELU),
+// and the shape with the least of it is taken (rows: the caller's estimate, or the capacity).  Large tiles need the fewest
+// operand bytes per product and suit long contractions, small ones fill the chip when rows are few, the heights in between
+// are there because a round is paid whole (12 544 x 768 x 3072: 52 us in 237 tiles of 160 rows, 61 in 147 of 256), and two
+// groups of up to 192 x 96 suit short contractions and GELU, where the epilogue is a large part: 12 608 x 1536 x 384 with
+// GELU takes 31.4 us in tiles of 256 x 160, 27.2 in pairs of 128 x 128; 12 608 x 3072 x 768 with GELU 78.5 in 256 x 224, 69.9
+// in pairs of 192 x 96; 12 608 x 768 x 3072 52.9 in 256 x 160, 68 in pairs of 128 x 128.
+// The constants are a least-squares fit to 29 row counts from 20 to 50 432 at the four layers of 768-, 384- and 192-wide blocks
+// in both types (per shape; where it is within 40 % of the fastest); the shape taken is 0.5 % slower than the fastest of all
+// on average and 12 % at most.
 constexpr int kCus = 256;
-constexpr int kGeluNs = 80;                                    // per nj * mt
-struct TileShape { int nj, mt, step_ns, tile_ns; };
+constexpr int kGeluNs = 85, kPairGeluNs = 62;                  // per nj * mt of a tile, of a pair of tiles
+struct TileShape { int nj, mt, per_cu, step_ns, tile_ns, pair_step_ns, pair_tile_ns; };
 constexpr TileShape kTileShapes[] = {
-    {8, 8, 1040, 6000}, {8, 7, 900, 5800}, {8, 6, 800, 5300}, {8, 5, 670, 4700}, {8, 4, 580, 3300},
-    {6, 4, 475, 2600}, {6, 3, 410, 1700}, {6, 2, 385, 1000}, {4, 4, 375, 1600}, {4, 3, 340, 1100},
-    {4, 2, 300, 600}, {2, 4, 290, 800}, {2, 2, 235, 600}, {2, 1, 180, 500}};
+    {8, 8, 1, 1320, 6660, 0, 0}, {8, 7, 1, 1140, 6260, 0, 0}, {8, 6, 1, 1010, 5790, 0, 0}, {8, 5, 1, 880, 4470, 0, 0},
+    {8, 4, 1, 730, 3740, 0, 0}, {6, 4, 1, 600, 2650, 0, 0}, {6, 2, 1, 380, 1610, 0, 0}, {4, 4, 1, 425, 1890, 0, 0},
+    {4, 3, 1, 365, 1500, 0, 0}, {2, 1, 1, 150, 620, 0, 0},
+    {6, 3, 2, 530, 1600, 900, 3700}, {4, 4, 2, 490, 1100, 830, 3300}, {4, 2, 2, 290, 680, 545, 1630},
+    {2, 4, 2, 265, 890, 555, 1660}, {2, 2, 2, 190, 560, 340, 1070}};
 // rows: the caller's estimate, or the capacity
 inline TileShape pick_linear_shape(int rows, int N, int K, int act) {
-    TileShape pick{2, 2, 0, 0};                                // N is a multiple of 64: this one always fits
+    TileShape pick = kTileShapes[sizeof(kTileShapes) / sizeof(kTileShapes[0]) - 1];        // N is a multiple of 64: this one always fits
     int64_t best = INT64_MAX;
     for (const TileShape& c : kTileShapes) {
         if (N % (32 * c.nj) != 0) continue;
         const int64_t tiles = (int64_t)((rows + 32 * c.mt - 1) / (32 * c.mt)) * (N / (32 * c.nj));
-        const int64_t cost = (tiles + kCus - 1) / kCus * (K / kTK * c.step_ns + c.tile_ns + (act == 1 ? kGeluNs * c.nj * c.mt : 0));
+        const int64_t n = (tiles + kCus - 1) / kCus, pairs = c.per_cu == 2 ? n / 2 : 0;
+        const int ksteps = K / kTK, gelu = act == 1 ? c.nj * c.mt : 0;
+        const int64_t cost = (n - 2 * pairs) * (ksteps * c.step_ns + c.tile_ns + kGeluNs * gelu) +
+                             pairs * (ksteps * c.pair_step_ns + c.pair_tile_ns + kPairGeluNs * gelu);
         if (cost < best) { best = cost; pick = c; }
     }
     return pick;
@@ -137,13 +149,13 @@ inline TileShape pick_linear_shape(int rows, int N, int K, int act) {
 constexpr int kPanel = 6;
 struct LinearGrid {
     int n_tiles, panel, last, groups;                          // last: width of the last panel
-    LinearGrid(int nj, int mt, int rows_cap, int N) {
+    LinearGrid(int nj, int mt, int per_cu, int rows_cap, int N) {
         n_tiles = N / (32 * nj);
         const int panels = (n_tiles + kPanel - 1) / kPanel;
         panel = (n_tiles + panels - 1) / panels;
         last = n_tiles - (n_tiles - 1) / panel * panel;
         const int64_t tiles = (int64_t)((rows_cap + 32 * mt - 1) / (32 * mt)) * n_tiles;
-        groups = (int)(tiles < kCus ? (tiles + kLinearXcds - 1) / kLinearXcds * kLinearXcds : kCus);
+        groups = (int)(tiles < kCus * per_cu ? (tiles + kLinearXcds - 1) / kLinearXcds * kLinearXcds : kCus * per_cu);
     }
 };
 

@@ -19,30 +19,33 @@ def lib() -> ctypes.CDLL:
         return ctypes.CDLL(so)
 
 
-# tiles of 32 nj features x 32 mt rows
-SHAPES = [(8, 8), (8, 7), (8, 6), (8, 5), (8, 4), (6, 4), (6, 3), (6, 2), (4, 4), (4, 3), (4, 2), (2, 4), (2, 2), (2, 1)]
+# tiles of 32 nj features x 32 mt rows, per_cu work-groups on a CU
+SHAPES = [(8, 8, 1), (8, 7, 1), (8, 6, 1), (8, 5, 1), (8, 4, 1), (6, 4, 1), (6, 2, 1), (4, 4, 1), (4, 3, 1), (2, 1, 1),
+          (6, 3, 2), (4, 4, 2), (4, 2, 2), (2, 4, 2), (2, 2, 2)]
 
 
-def shapes():
-    """[(nj, mt, LDS stages)] as the library has them."""
-    out = (ctypes.c_int * 3)()
-    res = []
+@functools.lru_cache(None)
+def stages():
+    """{(nj, mt, per_cu): LDS stages} as the library has them, in its order."""
+    out = (ctypes.c_int * 4)()
+    res = {}
     for i in range(lib().linear_shape_count()):
         lib().linear_shape(i, out)
-        res.append(tuple(out))
+        res[tuple(out[:3])] = out[3]
     return res
 
 
 def pick(rows_hint, rows, N, K, act):
-    """(nj, mt, tiles) of a call over `rows` rows with this row estimate."""
-    out = (ctypes.c_int * 3)()
+    """((nj, mt, per_cu), tiles) of a call over `rows` rows with this row estimate."""
+    out = (ctypes.c_int * 4)()
     lib().linear_pick(rows_hint, rows, N, K, {"none": 0, "gelu": 1}[act], out)
-    return tuple(out)
+    return tuple(out[:3]), out[3]
 
 
 @functools.lru_cache(None)
-def call_for(nj, mt, act, K):
-    """(rows_hint, N) with the fewest outputs for which the rule picks this shape."""
+def call_for(shape, act, K):
+    """(rows_hint, N) with the fewest outputs for which the rule picks this shape, or None."""
+    nj, mt, _ = shape
     best = None
     for n_tiles in range(1, 65):
         N = 32 * nj * n_tiles
@@ -50,6 +53,15 @@ def call_for(nj, mt, act, K):
             break
         for m_tiles in range(1, 513):
             for hint in (32 * mt * m_tiles - 31, 32 * mt * m_tiles):
-                if (best is None or hint * N < best[0] * best[1]) and hint * N <= 1 << 25 and pick(hint, hint, N, K, act)[:2] == (nj, mt):
+                if (best is None or hint * N < best[0] * best[1]) and hint * N <= 1 << 25 and pick(hint, hint, N, K, act)[0] == shape:
                     best = (hint, N)
     return best
+
+
+def call_beyond_the_ring(shape, act):
+    """(rows_hint, N, K): the same with at least two steps more than the LDS ring has stages."""
+    for K in (64 * (stages()[shape] + 2), 768, 1536, 3072):
+        found = call_for(shape, act, K)
+        if found:
+            return (*found, K)
+    raise AssertionError(f"no call takes {shape}")

@@ -31,10 +31,10 @@ int check_loads(const LinearCursor& c, int tile_rows, int64_t end, uint32_t row_
     return kOk;
 }
 
-template <int NJ, int MT>
+template <int NJ, int MT, int PER_CU>
 int check(int rows_cap, int rows, int N, int K) {
-    typedef LinearShape<NJ, MT> S;
-    const LinearGrid grid(NJ, MT, rows_cap, N);
+    typedef LinearShape<NJ, MT, PER_CU> S;
+    const LinearGrid grid(NJ, MT, PER_CU, rows_cap, N);
     const uint32_t row_bytes = (uint32_t)K * 2u;
     const int ksteps = K / kTK;
     const int64_t valid = rows < 0 ? 0 : rows;
@@ -78,8 +78,8 @@ int check(int rows_cap, int rows, int N, int K) {
 
 extern "C" {
 
-int linear_walk_check(int nj, int mt, int rows_cap, int rows, int N, int K) {
-#define CASE(NJ, MT) if (nj == NJ && mt == MT) return check<NJ, MT>(rows_cap, rows, N, K);
+int linear_walk_check(int nj, int mt, int per_cu, int rows_cap, int rows, int N, int K) {
+#define CASE(NJ, MT, PER_CU) if (nj == NJ && mt == MT && per_cu == PER_CU) return check<NJ, MT, PER_CU>(rows_cap, rows, N, K);
     LINEAR_SHAPES(CASE)
 #undef CASE
     return -1;
@@ -87,25 +87,26 @@ int linear_walk_check(int nj, int mt, int rows_cap, int rows, int N, int K) {
 
 int linear_shape_count(void) {
     int n = 0;
-#define CASE(NJ, MT) ++n;
+#define CASE(NJ, MT, PER_CU) ++n;
     LINEAR_SHAPES(CASE)
 #undef CASE
     return n;
 }
 
-// {nj, mt, LDS stages} of shape i
+// {nj, mt, per_cu, LDS stages} of shape i
 void linear_shape(int i, int* out) {
-#define CASE(NJ, MT) if (i-- == 0) { out[0] = NJ; out[1] = MT; out[2] = LinearShape<NJ, MT>::kStages; }
+#define CASE(NJ, MT, PER_CU) if (i-- == 0) { out[0] = NJ; out[1] = MT; out[2] = PER_CU; out[3] = LinearShape<NJ, MT, PER_CU>::kStages; }
     LINEAR_SHAPES(CASE)
 #undef CASE
 }
 
-// {nj, mt, tiles of a call over `rows` rows} of the shape that the rule picks
+// {nj, mt, per_cu, tiles of a call over `rows` rows} of the shape that the rule picks
 void linear_pick(int rows_hint, int rows, int N, int K, int act, int* out) {
     const TileShape c = pick_linear_shape(rows_hint, N, K, act);
     out[0] = c.nj;
     out[1] = c.mt;
-    out[2] = (rows + 32 * c.mt - 1) / (32 * c.mt) * (N / (32 * c.nj));
+    out[2] = c.per_cu;
+    out[3] = (rows + 32 * c.mt - 1) / (32 * c.mt) * (N / (32 * c.nj));
 }
 
 }  // extern "C"

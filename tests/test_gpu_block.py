@@ -215,16 +215,14 @@ def test_gelu_of_every_value_to_a_relative_bound(dtype):
 
 
 @pytest.mark.parametrize("residual", [False, True])
-@pytest.mark.parametrize("nj,mt", rule.SHAPES)
-def test_gelu_keeps_nan_and_infinities(nj, mt, residual):
+@pytest.mark.parametrize("shape", rule.SHAPES)
+def test_gelu_keeps_nan_and_infinities(shape, residual):
     """GELU(NaN) = NaN, GELU(inf) = inf and GELU(-inf) = 0 (the limit) in every tile shape, from a bias and from an input row;
     everything beside them is as without them."""
-    stages = {s[:2]: s[2] for s in rule.shapes()}[nj, mt]
-    K = 64 * (stages + 2)
-    hint, N = rule.call_for(nj, mt, "gelu", K)
-    dtype = ("f16", "bf16")[(nj + mt + residual) % 2]
+    hint, N, K = rule.call_beyond_the_ring(shape, "gelu")
+    dtype = ("f16", "bf16")[(sum(shape) + residual) % 2]
     tdt = _TD[dtype]
-    rows = 32 * mt + 1
+    rows = 32 * shape[1] + 1
     cap = max(rows, hint)
     x, w, b = _rand((rows, K), 1, tdt), _rand((N, K), 2, tdt, K ** -0.5), _rand((N,), 3, tdt, 0.5)
     r = _rand((rows, N), 4, tdt)

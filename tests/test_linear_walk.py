@@ -8,32 +8,33 @@ _FAULT = {1: "a tile is taken twice", 2: "a tile is missed", 3: "loads of the wr
           5: "a load reads past the end", 6: "work without rows"}
 
 
-def follow(nj, mt, rows, N, K, cap=None):
-    fault = rule.lib().linear_walk_check(nj, mt, max(rows, 1) if cap is None else cap, rows, N, K)
-    assert fault == 0, (_FAULT.get(fault, fault), nj, mt, rows, N, K, cap)
+def follow(shape, rows, N, K, cap=None):
+    fault = rule.lib().linear_walk_check(*shape, max(rows, 1) if cap is None else cap, rows, N, K)
+    assert fault == 0, (_FAULT.get(fault, fault), shape, rows, N, K, cap)
 
 
 def test_shapes_are_the_library_s():
-    assert [(nj, mt) for nj, mt, _ in rule.shapes()] == rule.SHAPES
+    assert list(rule.stages()) == rule.SHAPES
 
 
-@pytest.mark.parametrize("nj,mt", rule.SHAPES)
-def test_every_load_stays_inside_its_operand(nj, mt):
-    stages = {s[:2]: s[2] for s in rule.shapes()}[nj, mt]
-    tm, tn = 32 * mt, 32 * nj
+@pytest.mark.parametrize("shape", rule.SHAPES)
+def test_every_load_stays_inside_its_operand(shape):
+    stages = rule.stages()[shape]
+    tm, tn = 32 * shape[1], 32 * shape[0]
     for K in (64, 128, 64 * (stages - 1), 64 * (stages + 2), 768):
         for rows in (1, tm - 1, tm, tm + 1, 3 * tm + 17, 9 * tm + 1):
             for feature_tiles in (1, 3, 7, 13):
-                follow(nj, mt, rows, tn * feature_tiles, K)
-        follow(nj, mt, 40 * tm + 5, tn * 20, K)                 # several tiles per work-group
-        follow(nj, mt, tm + 3, tn * 2, K, cap=50 * tm)          # far fewer rows than the capacity
-    follow(nj, mt, 2 * tm + 1, tn, 1 << 22)                     # the widest rows there are
-    follow(nj, mt, 0, tn * 3, 768, cap=tm)
+                follow(shape, rows, tn * feature_tiles, K)
+        follow(shape, 40 * tm + 5, tn * 20, K)                 # several tiles per work-group
+        follow(shape, tm + 3, tn * 2, K, cap=50 * tm)          # far fewer rows than the capacity
+    follow(shape, 2 * tm + 1, tn, 1 << 22)                     # the widest rows there are
+    follow(shape, 0, tn * 3, 768, cap=tm)
 
 
-@pytest.mark.parametrize("nj,mt", rule.SHAPES)
-def test_a_negative_device_row_count_is_no_work(nj, mt):
+@pytest.mark.parametrize("shape", rule.SHAPES)
+def test_a_negative_device_row_count_is_no_work(shape):
     """The number of tiles of such a count must not wrap round to a positive one."""
+    nj, mt, _ = shape
     for rows in (-1, -32 * mt, -32 * mt - 1, -(1 << 30), -(1 << 31) + 1, -(1 << 31)):
         for n_tiles in (1, 24, 33, 48, 63, 64, 96, 128, 512):
-            follow(nj, mt, rows, 32 * nj * n_tiles, 64, cap=300)
+            follow(shape, rows, 32 * nj * n_tiles, 64, cap=300)
