@@ -8,6 +8,7 @@ been built, loading raises.
 from __future__ import annotations
 
 import ctypes
+import warnings
 from pathlib import Path
 
 import torch
@@ -79,20 +80,35 @@ def load() -> ctypes.CDLL:
     return _lib
 
 
+class _Ctypes:
+    """The entry points through ctypes, without the native side: every argument is checked in Python (dev passes none) and
+    converted by ctypes."""
+
+    @staticmethod
+    def dev(t, dtype, shape):
+        return None
+
+    def __getattr__(self, name):
+        return getattr(load(), name)
+
+
 _marshal = None
 
 
 def _native():
-    """The native side of a checked call (native/marshal.cpp): tensor checks and the entry points with argument conversion."""
+    """The native side of a checked call (native/marshal.cpp): tensor checks and the entry points with argument conversion.
+    It is tied to the torch and the Python it was built for; elsewhere the same library is called through ctypes, which takes
+    some 6 us more a call and is said once."""
     global _marshal
     if _marshal is None:
         load()
         try:
             from paper_2604_15408_amd import _ragged_marshal
+            _marshal = _ragged_marshal
         except ImportError as e:
-            raise FileNotFoundError(f"{_PKG / '_ragged_marshal.so'} is missing or was built for another torch: build it with "
-                                    "`python -m paper_2604_15408_amd.build` (there is no fallback implementation)") from e
-        _marshal = _ragged_marshal
+            warnings.warn(f"{_PKG / '_ragged_marshal.so'} is missing or was built for another torch ({e}); checked calls go through "
+                          "ctypes, which is slower: build it with `python -m paper_2604_15408_amd.build`", RuntimeWarning, stacklevel=3)
+            _marshal = _Ctypes()
     return _marshal
 
 
@@ -104,10 +120,15 @@ def version() -> int:
     return int(load().ragged_version())
 
 
+# The current stream without building a Stream object (0.3 instead of 1.1 us), where this torch has these two.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
-        if torch.cuda.is_initialized():                         # the same stream without building a Stream object (0.3 of 1.1 us)
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream is not None and _raw_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_raw_device())
         return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 

@@ -65,9 +65,13 @@ def build(verbose: bool = False, extra_flags=()) -> Path:
     if res.returncode != 0:
         raise RuntimeError(f"link failed:\n{res.stderr}")
     os.replace(tmp, LIB)
-    build_marshal()
     build_call_cost(hipcc)
     build_ceilings(hipcc)
+    try:
+        build_marshal()
+    except (RuntimeError, OSError) as e:                       # no C++ compiler, no torch or Python headers: ctypes serves (binding.py)
+        MARSHAL.unlink(missing_ok=True)                        # (not one of an older build)
+        print(f"warning: {e}\nchecked calls will go through ctypes, which is slower", file=sys.stderr)
     return LIB
 
 

@@ -235,3 +235,49 @@ def test_native_check_leaves_other_tensors_to_the_python_checks(lib):
         assert native.dev(t, None, None) is None
     with pytest.raises(TypeError, match="x must be a GPU tensor"):
         binding._dev(torch.zeros(2, 3), "x")
+
+
+@pytest.fixture
+def without_native(monkeypatch):
+    """A Python for which the native side was not built."""
+    import sys
+
+    import paper_2604_15408_amd as pkg
+    monkeypatch.setattr(binding, "_marshal", None)
+    monkeypatch.setitem(sys.modules, "paper_2604_15408_amd._ragged_marshal", None)      # its import raises ImportError
+    monkeypatch.delattr(pkg, "_ragged_marshal", raising=False)
+
+
+def test_calls_without_the_native_side(lib, without_native):
+    """The same entry points, checks and messages through ctypes, with one warning."""
+    import torch
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        native = binding._native()
+    for name in binding.EXPORTS:
+        fn = getattr(lib, name)
+        if fn.restype is not ctypes.c_int or name == "ragged_version":
+            continue
+        args = tuple(FAKE if t is ctypes.c_void_p else -1 for t in fn.argtypes)
+        assert getattr(native, name)(*args) == fn(*args) != 0, name
+    with pytest.raises(binding.RaggedError):
+        binding.ragged_noop(0, stream=0)
+    with pytest.raises(TypeError, match="x must be a GPU tensor"):
+        binding._dev(torch.zeros(2, 3), "x")
+
+
+def test_build_without_a_cpp_compiler(monkeypatch, tmp_path, capsys):
+    """The library is built all the same; an extension of an older build does not stay behind."""
+    from paper_2604_15408_amd import build as b
+    monkeypatch.setattr(b, "BUILD_DIR", tmp_path)
+    monkeypatch.setattr(b, "LIB", tmp_path / "lib.so")
+    monkeypatch.setattr(b, "CALL_COST", tmp_path / "call_cost")
+    monkeypatch.setattr(b, "CEILINGS", tmp_path / "ceilings.so")
+    monkeypatch.setattr(b, "MARSHAL", tmp_path / "marshal.so")
+    (tmp_path / "marshal.so").write_text("stale")
+    monkeypatch.setattr(b, "SOURCES", ["ragged_api.hip"])
+    monkeypatch.setattr(b, "build_call_cost", lambda hipcc: None)
+    monkeypatch.setattr(b, "build_ceilings", lambda hipcc: None)
+    for cxx in (str(tmp_path / "no-such-compiler"), "/bin/false"):
+        monkeypatch.setenv("CXX", cxx)
+        assert b.build() == b.LIB and b.LIB.exists() and not b.MARSHAL.exists()
+        assert "ctypes" in capsys.readouterr().err

@@ -284,3 +284,32 @@ def test_checked_calls_refuse_what_they_refused():
     assert binding._stream(None) == torch.cuda.current_stream().cuda_stream
     with pytest.raises(Exception):
         torch.vmap(lambda t: (dev(t, "x"), t)[1])(x)
+
+
+def test_checked_and_prepared_calls_without_the_native_side(monkeypatch):
+    """Where the extension cannot be imported, the same calls go through ctypes: same checks, same outputs."""
+    import sys
+
+    import paper_2604_15408_amd as pkg
+    w = wl.tiny()
+    x, keep = w.features().to(DEV), w.keep.to(DEV)
+    B, N, C = x.shape
+
+    def outputs():
+        packed = torch.zeros(B * N, C, dtype=x.dtype, device=DEV)
+        cu = torch.zeros(B + 1, dtype=torch.int32, device=DEV)
+        gidx = torch.zeros(B * N, dtype=torch.int32, device=DEV)
+        binding.ragged_pack(x, keep, packed, cu, gidx)
+        out = torch.zeros(B, N, C, dtype=x.dtype, device=DEV)
+        binding.prepare_unpack(packed, keep, cu, gidx, out, 1)()
+        torch.cuda.synchronize()
+        return packed, cu, gidx, out
+    want = outputs()
+    monkeypatch.setattr(binding, "_marshal", None)
+    monkeypatch.setitem(sys.modules, "paper_2604_15408_amd._ragged_marshal", None)
+    monkeypatch.delattr(pkg, "_ragged_marshal", raising=False)
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        got = outputs()
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+    with pytest.raises(ValueError, match="^x must be contiguous"):
+        binding._dev(x[:, :, ::2], "x")
