@@ -79,33 +79,59 @@ def test_linear_device_row_count():
 
 
 @pytest.mark.parametrize("dtype,act,residual", [("f16", "none", False), ("bf16", "gelu", True)])
-def test_linear_every_launch_shape(dtype, act, residual):
-    """The launch shape follows the expected row count (the capacity, or the caller's hint): 256 x 256
-    tiles for many rows or a long k-loop, 64 x 64 tiles with the k-loop split in two for few rows, 128 x 128
-    tiles between.  Large capacities with a small device row count keep the oracle's work small."""
+def test_linear_row_estimates(dtype, act, residual):
+    """The tile shape follows the expected row count (the capacity, or the caller's estimate): the same rows of a large buffer
+    under several estimates, in a different shape each, and a few calls without one, one of them with an odd number of k-steps."""
     kw = dict(dtype=dtype, act=act, residual=residual)
-    check_linear(700, 1024, 256, rows=700, cap=26000, seed=5, **kw)               # 408 tiles of 256 x 256
-    check_linear(300, 1024, 2048, rows=300, cap=8200, seed=6, **kw)               # long k-loop, 132 such tiles
-    check_linear(700, 1024, 256, rows=700, cap=26000, seed=5, hint=3000, **kw)    # 192 tiles of 128 x 128
-    check_linear(700, 1024, 256, rows=700, cap=26000, seed=5, hint=700, **kw)     # 64 x 64 tiles, k split
-    check_linear(130, 128, 3072, seed=7, **kw)                                    # 64 x 64 tiles, 24 k-steps per half
-    check_linear(700, 1024, 192, rows=650, cap=800, seed=8, hint=650, **kw)       # odd number of k-steps: no split
+    picked = set()
+    for hint in (0, 3000, 700):
+        picked.add(rule.pick(hint or 26000, 700, 1024, 256, act)[0])
+        check_linear(700, 1024, 256, rows=700, cap=26000, seed=5, hint=hint, **kw)
+    assert len(picked) == 3, picked
+    check_linear(300, 1024, 2048, rows=300, cap=8200, seed=6, **kw)
+    check_linear(130, 128, 3072, seed=7, **kw)
+    check_linear(700, 1024, 192, rows=650, cap=800, seed=8, hint=650, **kw)
 
 
-@pytest.mark.parametrize("hint,N,K", [
-    (3600, 4096, 64), (3100, 4096, 128), (3400, 3072, 128), (2100, 4096, 256), (2700, 2304, 128),   # 256 features x 256 .. 128 rows
-    (3100, 1536, 192), (5500, 576, 64), (1800, 1152, 64),                                           # 192 features x 128, 96, 64 rows
-    (2700, 1152, 128), (4100, 512, 64), (900, 1152, 64),                                            # 128 features x 128, 96, 64 rows
-    (1800, 576, 64), (9000, 64, 64), (100, 64, 64), (300, 128, 1024)])                              # 64 features x 128, 64, 32 rows
-def test_linear_every_tile_shape(hint, N, K):
-    """Each tile shape (picked through the row estimate) at row counts that end just before, on and just behind a tile
-    edge; one k-step, fewer and more k-steps than the LDS ring has stages; several tiles per work-group."""
-    for i, rows in enumerate((1, 127, 193, 258)):
-        check_linear(rows, N, K, dtype=("f16", "bf16")[i % 2], act=("none", "gelu")[i // 2], residual=i % 2 == 0,
-                     rows=rows, cap=hint, seed=50 + i, hint=hint)
-    if N <= 1536:
-        check_linear(hint, N, 64, seed=60, residual=True)
-        check_linear(130, N, 768, rows=129, cap=hint, seed=61, hint=hint)
+@pytest.mark.parametrize("act", ["none", "gelu"])
+@pytest.mark.parametrize("residual", [False, True])
+@pytest.mark.parametrize("shape", rule.SHAPES)
+def test_linear_every_tile_shape(shape, residual, act):
+    """Each tile shape, in both types: a contraction at least two steps longer than its LDS ring, so that what the main loop
+    loads is used, at row counts just before, on and just behind a tile edge, and at one where every work-group takes several
+    tiles; where the rule takes the shape at K = 64 too, several tiles of a single step each.  The whole launch runs; the oracle
+    checks rows around the edges of the first, second and last tile and some between."""
+    nj, mt, per_cu = shape
+    tm = 32 * mt
+    calls = [(*rule.call_beyond_the_ring(shape, act), rows) for rows in (tm - 1, tm, tm + 1, None)]
+    assert all(K // 64 >= rule.stages()[shape] + 2 for _, _, K, _ in calls)
+    if rule.call_for(shape, act, 64):
+        calls.append((*rule.call_for(shape, act, 64), 64, None))
+    for dtype in ("f16", "bf16"):
+        tdt = _TD[dtype]
+        for hint, N, K, rows in calls:
+            if rows is None:                                    # 1.3 and more tiles for each place, the last one partial
+                rows = tm * (330 * per_cu // (N // (32 * nj)) + 1) + tm // 2 + 1
+                assert rule.pick(hint, rows, N, K, act)[1] > 256 * per_cu
+            assert rule.pick(hint, rows, N, K, act)[0] == shape
+            cap = max(rows, hint)
+            x, w, b = _rand((cap, K), rows, tdt), _rand((N, K), 21, tdt, K ** -0.5), _rand((N,), 22, tdt, 0.5)
+            r = _rand((cap, N), 23, tdt) if residual else None
+            y = torch.full((cap, N), 77.0, dtype=tdt, device=DEV)
+            binding.ragged_linear(x.to(DEV), w.to(DEV), b.to(DEV), None if r is None else r.to(DEV), y,
+                                  torch.tensor([rows], dtype=torch.int32, device=DEV), act, rows_hint=hint)
+            torch.cuda.synchronize()
+            assert torch.all(y[rows:] == 77.0), "rows past the device row count were written"
+            assert not torch.any(y[:rows] == 77.0), "some output element was never written"
+            last = (rows - 1) // tm * tm
+            near = {e + d for e in (0, tm // 2, tm, last) for d in (-1, 0, 1, 15, 16, 17)} | {rows - 2, rows - 1}
+            pick = sorted(v for v in near if 0 <= v < rows)
+            want = oracle.linear(wl.to_words(x[pick]), wl.to_words(w), wl.to_words(b), None if r is None else wl.to_words(r[pick]), act, dtype,
+                                 threads=oracle.max_threads())
+            S = oracle.linear(wl.to_words(x[pick].abs()), wl.to_words(w.abs()), dtype=dtype, threads=oracle.max_threads())
+            err = np.abs(y[pick].cpu().to(torch.float64).numpy() - want)
+            bound = _ULP[dtype] * np.abs(want) + 2.0 ** -15 * S + 1e-6
+            assert np.all(err <= bound), (shape, dtype, N, K, rows, float((err / bound).max()))
 
 
 @pytest.mark.parametrize("M", [12608, 6304])
