@@ -725,6 +725,7 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
         wait_vm<0>();
         __syncthreads();
     };
+    static_assert(kRing == 2, "slots alternate, and a tile is waited for with nothing behind it");
     int slot = 0;                           // ring slot of tile t
     if constexpr (PEEL) {
         // The first tile, full ones, the last.  The loop in the middle knows only one form of a tile, so its accumulators stay

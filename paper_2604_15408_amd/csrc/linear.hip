@@ -74,11 +74,9 @@ void layernorm_kernel(const uint16_t* x, const uint16_t* __restrict__ gamma,    
     for (int i = 0; i < kLnChunks; ++i) {
         const int c = lane + kWaveSize * i;
         if (c < chunks) {
-            float t[16];
-            const uint4 raw = raw_x[i];
-            unpack16(In{}, raw, raw, t);
+            unpack8(In{}, raw_x[i], v[i]);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) { v[i][e] = t[e]; sum += t[e]; }
+            for (int e = 0; e < 8; ++e) sum += v[i][e];
         } else {
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[i][e] = 0.f;
@@ -97,15 +95,12 @@ void layernorm_kernel(const uint16_t* x, const uint16_t* __restrict__ gamma,    
     for (int i = 0; i < kLnChunks; ++i) {
         const int c = lane + kWaveSize * i;
         if (c < chunks) {
-            float gm[16], bt[16], o16[16];
-            const uint4 graw = raw_g[i], braw = raw_b[i];
-            unpack16(In{}, graw, graw, gm);
-            unpack16(In{}, braw, braw, bt);
+            float gm[8], bt[8], out[8];
+            unpack8(In{}, raw_g[i], gm);
+            unpack8(In{}, raw_b[i], bt);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o16[e] = o16[8 + e] = __builtin_fmaf((v[i][e] - mean) * rstd, gm[e], bt[e]);
-            uint4 lo, hi;
-            pack16(In{}, o16, lo, hi);
-            dst[c] = lo;
+            for (int e = 0; e < 8; ++e) out[e] = __builtin_fmaf((v[i][e] - mean) * rstd, gm[e], bt[e]);
+            dst[c] = pack8(In{}, out);
         }
     }
 }

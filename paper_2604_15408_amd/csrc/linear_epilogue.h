@@ -1,5 +1,4 @@
-// What the linear kernels share behind their main loops: GELU and the conversion of 16 consecutive outputs
-// (internal).
+// What the linear layers and LayerNorm share: GELU and the conversion of 8 consecutive values of a row (internal).
 #pragma once
 
 #include "common.h"
@@ -35,32 +34,7 @@ __device__ __forceinline__ float gelu_erf(float t) {
     return __builtin_fmaf(-a, __builtin_amdgcn_exp2f(p), __builtin_elementwise_maximum(t, 0.f));
 }
 
-__device__ __forceinline__ void unpack16(F16, const uint4& a, const uint4& b, float (&v)[16]) {
-    const f16x8 lo = as_vec8<f16x8>(a), hi = as_vec8<f16x8>(b);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { v[e] = (float)lo[e]; v[8 + e] = (float)hi[e]; }
-}
-__device__ __forceinline__ void unpack16(BF16, const uint4& a, const uint4& b, float (&v)[16]) {
-    const bf16x8 lo = as_vec8<bf16x8>(a), hi = as_vec8<bf16x8>(b);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { v[e] = (float)lo[e]; v[8 + e] = (float)hi[e]; }
-}
-__device__ __forceinline__ void pack16(F16, const float (&v)[16], uint4& a, uint4& b) {
-    f16x8 lo, hi;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { lo[e] = (_Float16)v[e]; hi[e] = (_Float16)v[8 + e]; }
-    a = __builtin_bit_cast(uint4, lo);
-    b = __builtin_bit_cast(uint4, hi);
-}
-__device__ __forceinline__ void pack16(BF16, const float (&v)[16], uint4& a, uint4& b) {
-    bf16x8 lo, hi;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { lo[e] = (__bf16)v[e]; hi[e] = (__bf16)v[8 + e]; }
-    a = __builtin_bit_cast(uint4, lo);
-    b = __builtin_bit_cast(uint4, hi);
-}
-
-// Eight consecutive outputs of one row <-> 16 bytes.
+// Eight consecutive values of one row <-> 16 bytes.
 __device__ __forceinline__ void unpack8(F16, const uint4& a, float (&v)[8]) {
     const f16x8 h = as_vec8<f16x8>(a);
 #pragma unroll

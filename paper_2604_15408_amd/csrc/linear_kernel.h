@@ -1,5 +1,6 @@
 // linear_kernel: y[m][n] = act( sum_k x[m][k] * w[n][k] + bias[n] ) (+ residual[m][n]) over packed rows, on MFMA
-// (internal; the rule that picks a tile shape and the walk over the tiles are in linear_walk.h, one source per input type instantiates the kernel).
+// (internal; the rule that picks a tile shape and the walk over the tiles are in linear_walk.h, one source per input type
+// instantiates the kernel).
 //
 // x [rows, K], w [N, K]: both operands are contiguous along k, which is how an MFMA lane wants them (8 consecutive k per
 // 16-byte read).  The product is formed transposed (features x tokens: w is the A operand), and MFMA row m' of feature
@@ -59,7 +60,7 @@ struct LinearArgs {
     uint32_t panel_magic, last_magic;            // div_magic() of panel and of the last panel's width
 };
 
-#define ALWAYS_INLINE __attribute__((always_inline))
+#define RAGGED_INLINE_LAMBDA __attribute__((always_inline))
 
 // acc += A B (FIRST: acc = A B), the accumulator in the accumulation registers.
 #define MFMA_TEXT(dt) "v_mfma_f32_16x16x32_" dt " %0, %1, %2, "
@@ -169,17 +170,17 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
     u32x4 x_rsrc, w_rsrc;
     LinearCursor x_cur, w_cur;
     x_cur.tile = w_cur.tile = t_first;
-    auto set_rsrc = [&](u32x4& r, const uint16_t* base, uint32_t bytes) ALWAYS_INLINE {
+    auto set_rsrc = [&](u32x4& r, const uint16_t* base, uint32_t bytes) RAGGED_INLINE_LAMBDA {
         const uint64_t a = reinterpret_cast<uint64_t>(base);
         r[0] = __builtin_amdgcn_readfirstlane((uint32_t)a);
         r[1] = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
         r[2] = __builtin_amdgcn_readfirstlane(bytes);
         r[3] = 0x00020000u;
     };
-    auto set_x = [&]() ALWAYS_INLINE { set_rsrc(x_rsrc, p.x + (int64_t)x_cur.first * p.K, x_cur.bytes); };
-    auto set_w = [&]() ALWAYS_INLINE { set_rsrc(w_rsrc, p.w + (int64_t)w_cur.first * p.K, w_cur.bytes); };
-    auto next_x = [&]() ALWAYS_INLINE { if (x_cur.next<TM, TN, true>(walk, row_bytes)) set_x(); };
-    auto next_w = [&]() ALWAYS_INLINE { if (w_cur.next<TM, TN, false>(walk, row_bytes)) set_w(); };
+    auto set_x = [&]() RAGGED_INLINE_LAMBDA { set_rsrc(x_rsrc, p.x + (int64_t)x_cur.first * p.K, x_cur.bytes); };
+    auto set_w = [&]() RAGGED_INLINE_LAMBDA { set_rsrc(w_rsrc, p.w + (int64_t)w_cur.first * p.K, w_cur.bytes); };
+    auto next_x = [&]() RAGGED_INLINE_LAMBDA { if (x_cur.next<TM, TN, true>(walk, row_bytes)) set_x(); };
+    auto next_w = [&]() RAGGED_INLINE_LAMBDA { if (w_cur.next<TM, TN, false>(walk, row_bytes)) set_w(); };
 
     // ---- LDS addresses of this lane's operands: x (B operand) row 16 mt + col, w (A operand) of feature tile j: row
     // 32 (j/2) + 8 (col/4) + 4 (j%2) + col%4; chunk 2g + half
@@ -196,13 +197,13 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
     }
     f32x4 acc[NJ][MT];
     u32x4 a0[NJ], b0[MT], a1[NJ], b1[MT];
-    auto read_a = [&](int h, int j) ALWAYS_INLINE { return lds_vec(ra[h][j & 1] + (j >> 1) * 4096); };
-    auto read_b = [&](int h, int mt) ALWAYS_INLINE { return lds_vec(rb[h] + mt * 2048); };
+    auto read_a = [&](int h, int j) RAGGED_INLINE_LAMBDA { return lds_vec(ra[h][j & 1] + (j >> 1) * 4096); };
+    auto read_b = [&](int h, int mt) RAGGED_INLINE_LAMBDA { return lds_vec(rb[h] + mt * 2048); };
 
     constexpr int NS = NJ * MT;                                // products of half a step = issue slots
     static_assert(!TWO || NS >= 16, "the slots before the barrier of a half hold the address updates of two-stage rings");
     // ---- first half of a step: products of (a0, b0)
-    auto half_a = [&](auto first_tag, uint32_t fill, uint32_t delta) ALWAYS_INLINE {
+    auto half_a = [&](auto first_tag, uint32_t fill, uint32_t delta) RAGGED_INLINE_LAMBDA {
         constexpr bool FIRST = decltype(first_tag)::value;
         constexpr int kSync = TWO ? NS / 8 : 0, kLeft = NS - kSync;
 #pragma unroll
@@ -241,7 +242,7 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
         else next_w();
     };
     // ---- second half: products of (a1, b1); fragments of the next step
-    auto half_b = [&](uint32_t fill, uint32_t delta) ALWAYS_INLINE {
+    auto half_b = [&](uint32_t fill, uint32_t delta) RAGGED_INLINE_LAMBDA {
         constexpr int kReads = NJ + MT;
 #pragma unroll
         for (int m = 0; m < NS; ++m) {
@@ -273,7 +274,7 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
 
     int m0, n0;                                                // the tile being computed
     uint4 bias_raw[NJ / 2];
-    auto load_bias = [&]() ALWAYS_INLINE {
+    auto load_bias = [&]() RAGGED_INLINE_LAMBDA {
 #pragma unroll
         for (int jp = 0; jp < NJ / 2; ++jp)
             bias_raw[jp] = p.bias ? *reinterpret_cast<const uint4*>(p.bias + n0 + wn * 16 * NJ + 32 * jp + 8 * g) : make_uint4(0, 0, 0, 0);
@@ -309,12 +310,12 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
         for (int mt = 0; mt < MT; ++mt) b1[mt] = read_b(1, mt);
 
     // stage numbers: s of the current step, s_next of the next, fill_a / fill_b the ones that half A / B load into
-    auto wrap = [&](uint32_t s) ALWAYS_INLINE { return s == lds0 + (STAGES - 1) * kStageBytes ? lds0 : s + kStageBytes; };
+    auto wrap = [&](uint32_t s) RAGGED_INLINE_LAMBDA { return s == lds0 + (STAGES - 1) * kStageBytes ? lds0 : s + kStageBytes; };
     uint32_t s = lds0;
     uint32_t fill_a = TWO ? lds0 : lds0 + kAheadW * kStageBytes;
     uint32_t fill_b = TWO ? lds0 : lds0 + (kAheadX % STAGES) * kStageBytes;
     bool landed = false;
-    auto step = [&](auto first_tag) ALWAYS_INLINE {
+    auto step = [&](auto first_tag) RAGGED_INLINE_LAMBDA {
         const uint32_t s_next = wrap(s);
         const uint32_t delta = s_next - s;
         if (TWO) __builtin_amdgcn_s_waitcnt(0xC17F);           // lgkmcnt(1): all but the last fragment
@@ -349,16 +350,16 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
             walk.tile_of(t + stride, TM, TN, m0, n0);
             load_bias();                                       // the next tile's
         }
-        auto offset = [&](int mt) ALWAYS_INLINE -> int64_t {
+        auto offset = [&](int mt) RAGGED_INLINE_LAMBDA -> int64_t {
             const int m = m_base + 16 * mt;
             return (int64_t)(m < rows ? m : rows - 1) * N + n_base;
         };
-        auto finish = [&](auto act_tag, auto res_tag) ALWAYS_INLINE {
+        auto finish = [&](auto act_tag, auto res_tag) RAGGED_INLINE_LAMBDA {
             constexpr bool ACT = decltype(act_tag)::value, RES = decltype(res_tag)::value;
             constexpr int kMost = NJ == 8 ? (MT == 8 ? 2 : 3) : 4;
             constexpr int kAhead = kMost < MT ? kMost : MT;    // residual rows in flight
             uint4 r_raw[kAhead][NJ / 2];
-            auto load_res = [&](int mt) ALWAYS_INLINE {
+            auto load_res = [&](int mt) RAGGED_INLINE_LAMBDA {
                 const int64_t off = offset(mt);
 #pragma unroll
                 for (int jp = 0; jp < NJ / 2; ++jp) r_raw[mt % kAhead][jp] = *reinterpret_cast<const uint4*>(p.res + off + 32 * jp);
