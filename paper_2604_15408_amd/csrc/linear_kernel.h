@@ -7,29 +7,33 @@
 // tile j stands for feature 32*(j/2) + 8*(m'/4) + 4*(j%2) + m'%4, so that a lane ends up with 8 consecutive features of a
 // token and the four lanes of a token store 64 contiguous bytes.
 //
-// One work-group of four wavefronts per CU, one wavefront per SIMD, each owning 16 NJ features x 16 MT tokens: with the
-// whole register file to itself a wavefront holds up to 128 x 128 accumulators, and LDS traffic per product is half of
-// that of eight wavefronts of 64 x 128, which kept the LDS pipe busy as long as the matrix core (25 216 rows, us before
-// and now: 2304 x 768 98 and 86, 768 x 3072 141 and 101; an 8192^3 product ran at 1.17 PFLOP/s and runs at 1.41).  Large
-// problems are bound by the clock the chip holds under that load (1.3 to 1.6 GHz at the K = 768 layers, with 90 % of the
-// cycles issuing matrix work), small ones by the time of a step (LDS round trip, barrier) and by launch and first loads.
+// A work-group has four wavefronts, one on each SIMD of a CU, each owning 16 NJ features x 16 MT tokens.  With a CU to itself
+// (PER_CU 1) a wavefront has the whole register file and holds up to 128 x 128 accumulators, and LDS traffic per product is
+// half of that of eight wavefronts of 64 x 128, which kept the LDS pipe busy as long as the matrix core (25 216 rows, us
+// before and now: 2304 x 768 102 and 86, 768 x 3072 144 and 102).  Its epilogue runs beside nothing, though.  With PER_CU 2 two
+// groups of up to 192 x 96 share the CU and one's epilogue runs beside the other's products, which is the faster form where
+// the contraction is short or the epilogue has GELU (12 608 x 1536 x 384 with GELU 31.7 -> 27.2, 25 216 x 3072 x 768 with GELU
+// 145 -> 130); linear_walk.h has the rule.  By the counters (fp16, us and share of the cycles with the matrix core busy):
+// 25 216 x 3072 x 768 without GELU 116 and 0.47, 12 608 x 768 x 3072 52 and 0.48, where a loop of products alone on this chip
+// sustains 0.50 to 0.56 of its rate; few rows are bound by the time of a step (LDS round trip, barrier) and by launch and
+// first loads (1334 x 768 x 3072 14 and 0.13, waiting 38 % of the time).
 //
-// With a single wavefront nothing else fills the gap an instruction leaves, so the loop is laid out by issue slots.
-// Measured: one instruction between two MFMAs is free, a second independent VALU too, anything more (or an address
-// computed in front of an LDS read) adds 4 cycles to the 16 of an MFMA, a load about 6.  So fragment reads have their
-// addresses ready (immediate offsets; the six registers move from stage to stage in slots of their own), a load's M0 set-up and the
-// load sit on the two sides of a product, and everything is spread evenly: a 256 x 256 step of 128 MFMAs takes 2300
-// cycles (2755 with reads and loads issued as they come).  The products are inline assembly: accumulators stay in the
-// accumulation registers without copies, and the order is kept.
+// With a single wavefront on a SIMD nothing else fills the gap an instruction leaves, so the loop is laid out by issue slots:
+// one instruction between two MFMAs is free, a second independent VALU too, anything more (or an address computed in front of
+// an LDS read) delays the next product.  So fragment reads have their addresses ready (immediate offsets; the six registers
+// move from stage to stage in slots of their own), a load's M0 set-up and the load sit on the two sides of a product, and
+// everything is spread evenly.  The products are inline assembly: accumulators stay in the accumulation registers without
+// copies, and the order is kept.
 //
 // Operand tiles (rows x 64 k = 128-byte rows) are brought into LDS by direct loads, row-major with the chunk swizzle
-// c ^ ((row>>1)&3) that makes every 16-byte fragment read conflict-free, in a ring of as many stages as fit 160 KB.
+// c ^ ((row>>1)&3) that spreads every 16-byte fragment read over all banks (8 cycles of the LDS pipe for 64 lanes), in a ring
+// of as many stages as fit 160 KB (PER_CU 2: half of it).
 // A step is two halves of 32 k; fragments of the next half are read while the products of this one run:
 //   * more than two stages: one barrier per step, between the halves.  The ring is refilled half a step at a time (w with
 //     the first half, x with the second);
-//   * two stages (tiles of 192 rows and more): x of both halves is held a step ahead, which frees the x part of a stage at
-//     the start of its step and the w part in the middle, so that its loads spread over the whole step as well (issued
-//     in one half they queue up: 4 x 16 KB at 64 bytes a cycle).
+//   * two stages (256 x 192 and more, and the pairs of 192 x 96 and 128 x 128): x of both halves is held a step ahead, which
+//     frees the x part of a stage at the start of its step and the w part in the middle, so that its loads spread over the
+//     whole step as well (issued in one half they queue up: 4 x 16 KB at 64 bytes a cycle).
 // The tiles of a work-group follow each other without a break: the last steps of one load the first of the next.
 //
 // Epilogue in registers: bias, GELU, residual, one rounding, 16-byte stores.
