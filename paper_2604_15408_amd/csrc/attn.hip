@@ -319,8 +319,12 @@ __device__ __forceinline__ void tile_any(int rem, bool ext_tile, uint32_t tile0,
 // Long bounds go in phases: q-tiles 0 .. phase_tiles-1 of a batch of 128 pairs after the other, then the next phase_tiles of
 // every batch, and so on (grid (128, phase_tiles, phases * batches)).  With 577 tokens 512 pairs hold 9 MB of K/V per XCD,
 // more than its L2, so a whole batch per q-tile fetched K/V again for every q-tile: B=32 dense, bf16 / fp16 attention 80 / 69 us,
-// in phases 72 / 60; without the loads the arithmetic alone takes 62 / 50.  In one phase (each batch to its end) heavily pruned
-// launches start their work behind the surplus tiles of the batches in front (3 to 12 % slower at keep 0.1).
+// in phases 72 / 60; without the loads the arithmetic alone takes 62 / 50.  Over 330 to 900 tokens and 384 to 1536 pairs phases
+// take 0.82 to 0.88 of the undivided time dense, 0.88 at keep 0.3, 0.94 to 0.99 at keep 0.1, where single launches are up to
+// 12 % slower: multiples of 256 pairs, which batches of 512 fit (1536 pairs of 400 tokens, packed 8.1 -> 9.1, padded 13.6 -> 14.9).
+// In one phase (each batch to its end) heavily pruned launches start their work behind the surplus tiles of the batches in
+// front (3 to 12 % slower at keep 0.1); in runs of 512 pairs that go through their phases before the next 512 begin, they are
+// on average 2 to 9 % slower at keep 0.1 to 0.3 than here.
 //
 // A work-group has four wavefronts of 16 queries each.  Wavefront w issues the loads of rows
 // 16w .. 16w+15 of every K and V tile (four instructions per tile); rows past the end of the
@@ -392,6 +396,7 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
         const int batches = (int)((unsigned)(pairs + kPhasePairs - 1) / kPhasePairs);
         for (; batch >= batches; batch -= batches) m_tile += phase_tiles;
         group = kPhasePairs;
+        if (LIST && m_tile * kBM >= n_tok) return;             // (a whole phase holds tiles past the bound; they count no mask)
     }
     const int pair = batch * group + blockIdx.x;
     if (pair >= pairs) return;
@@ -431,7 +436,7 @@ void attn_kernel(const void* __restrict__ index, int n_tok, int fill_mode, int H
         // group m takes every q_tiles-th pass of the group over the tokens, the groups without rows of their own
         // (most of them, when much is pruned) included, before they leave
         const bool zero_fill = fill_mode == 1;
-        const int fill_groups = phase_tiles < 0 ? (int)gridDim.y : (n_tok + phase_tiles * kBM - 1) / (phase_tiles * kBM) * phase_tiles;
+        const int fill_groups = phase_tiles < 0 ? (int)gridDim.y : (n_tok + kBM - 1) / kBM;
         // kStep, q-tile 0 (with short sequences: the groups that have rows): the count of the kept tokens in front of
         // the image shares the barrier of the length count, so the group knows s and n together.  The other q-tiles
         // count it after the test that lets most of them leave.

@@ -30,6 +30,7 @@ def run_padded(q, k, v, keep, scale, fill_mode, out_dtype=None, sentinel=55.0):
     (1, 1, 1, 1.0, "f16"), (2, 197, 3, 0.2, "f16"), (3, 197, 2, 1.0, "f16"), (4, 64, 2, 0.5, "bf16"),
     (2, 577, 2, 0.3, "f16"), (3, 300, 1, 0.02, "f16"), (2, 1100, 1, 0.1, "f16"), (5, 65, 12, 0.7, "bf16"),
     (58, 330, 9, 0.08, "f16"),                                  # q-tiles in phases
+    (58, 400, 9, 0.08, "bf16"), (58, 700, 9, 0.05, "f16"),      # ... of which the last holds tiles past the bound
 ])
 @pytest.mark.parametrize("fill_mode", [0, 1])
 def test_padded_parity(B, N, H, p, dtype, fill_mode):

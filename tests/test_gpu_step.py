@@ -105,7 +105,8 @@ def test_masks_beyond_16_kb():
     check(wl.Workload("b100w", 100, 197, 1, 64, "f16", 36, wl.keep_bernoulli(100, 197, 0.6, 13)), 0)
 
 
-@pytest.mark.parametrize("N,fill_mode,dtype", [(330, 1, torch.float16), (577, 0, torch.bfloat16), (577, 1, torch.float16)])
+@pytest.mark.parametrize("N,fill_mode,dtype", [(330, 1, torch.float16), (400, 1, torch.bfloat16), (700, 1, torch.float16),
+                                               (577, 0, torch.bfloat16), (577, 1, torch.float16)])
 def test_long_images_are_dispatched_in_phases(N, fill_mode, dtype):
     """More than 512 (image, head) pairs of more than 320 tokens: q-tiles in phases, the zero fill shared by all of them."""
     B, H = 58, 9
