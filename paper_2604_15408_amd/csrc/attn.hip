@@ -323,8 +323,8 @@ __device__ __forceinline__ void tile_any(int rem, bool ext_tile, uint32_t tile0,
 // take 0.82 to 0.88 of the undivided time dense, 0.88 at keep 0.3, 0.94 to 0.99 at keep 0.1, where single launches are up to
 // 12 % slower: multiples of 256 pairs, which batches of 512 fit (1536 pairs of 400 tokens, packed 8.1 -> 9.1, padded 13.6 -> 14.9).
 // In one phase (each batch to its end) heavily pruned launches start their work behind the surplus tiles of the batches in
-// front (3 to 12 % slower at keep 0.1); in runs of 512 pairs that go through their phases before the next 512 begin, they are
-// on average 2 to 9 % slower at keep 0.1 to 0.3 than here.
+// front (3 to 12 % slower at keep 0.1); in runs of 512 pairs that go through their phases before the next 512 begin,
+// packed ones are 6 to 9 % slower than here at keep 0.1 to 0.3, padded ones and the step 2 to 4 %.
 //
 // A work-group has four wavefronts of 16 queries each.  Wavefront w issues the loads of rows
 // 16w .. 16w+15 of every K and V tile (four instructions per tile); rows past the end of the
@@ -829,8 +829,9 @@ hipError_t launch_typed(const void* q, const void* k, const void* v, void* o,
     // Phases (see the kernel) where the bound allows more than kPhaseTiles q-tiles and the launch is more than the chip holds
     // at once.  Up to 512 pairs the tiles of the first phase are few enough for the first of every pair to be among the 1024
     // work-groups that start at once, which is all there is to do when much is pruned (577-token bound, B=32, keep 0.1: 4.9 us
-    // as before; 5.4 with five tiles); the modes with a mask, whose surplus groups have a mask to count, are not divided there
-    // (step of B=32, 577 tokens: keep 0.3 19.6 us undivided, 20.2 in phases).  Grids that phases would take past HIP's limits
+    // as before; 5.4 with five tiles; 385 to 512 pairs of 577 to 900 tokens in two tiles: 0.75 to 0.86 of the undivided time
+    // dense, the same at keep 0.3, 4 to 14 % more at keep 0.1); the modes with a mask, whose surplus groups have a mask to
+    // count, are not divided there (step of B=32, 577 tokens: keep 0.3 19.6 us undivided, 20.2 in phases).  Grids that phases would take past HIP's limits
     // are not divided either, nor up to 512 pairs bounds of up to 512 tokens (40 x 330, fp16: 34.4 us dense becomes 32.4, but
     // 4.2 at keep 0.1 becomes 4.7).
     const int full_batches = (pairs + kPhasePairs - 1) / kPhasePairs;
