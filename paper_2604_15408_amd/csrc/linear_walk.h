@@ -129,8 +129,12 @@ constexpr TileShape kTileShapes[] = {
     {4, 3, 1, 365, 1500, 0, 0}, {2, 1, 1, 150, 620, 0, 0},
     {6, 3, 2, 530, 1600, 900, 3700}, {4, 4, 2, 490, 1100, 830, 3300}, {4, 2, 2, 290, 680, 545, 1630},
     {2, 4, 2, 265, 890, 555, 1660}, {2, 2, 2, 190, 560, 340, 1070}};
+// Outputs and residual are reached by 32-bit offsets from a tile's first row (256 rows of 2^22 features are 2^31 bytes); wider
+// rows have a form of the smallest tile with 64-bit addresses.
+inline bool linear_is_wide(int N) { return N > 1 << 22; }
 // rows: the caller's estimate, or the capacity
 inline TileShape pick_linear_shape(int rows, int N, int K, int act) {
+    if (linear_is_wide(N)) return TileShape{2, 1, 1, 0, 0, 0, 0};
     TileShape pick = kTileShapes[sizeof(kTileShapes) / sizeof(kTileShapes[0]) - 1];        // N is a multiple of 64: this one always fits
     int64_t best = INT64_MAX;
     for (const TileShape& c : kTileShapes) {
