@@ -5,7 +5,7 @@
 // The linear kernel itself is in linear_kernel.h (instantiated per input type in linear_f16.hip and linear_bf16.hip); this
 // file launches it in the shape that linear_walk.h picks and holds LayerNorm.
 //
-// layernorm_kernel: one wavefront per row, the row held in registers, two passes (mean, then the
+// layernorm_kernel: 16, 32 or 64 lanes per row, the row held in registers, two passes (mean, then the
 //   biased variance of the centred values) in fp32.
 //
 // Rows: the caller passes a capacity and, optionally, a device pointer to the real row count (for
@@ -16,7 +16,7 @@
 namespace ragged {
 namespace {
 
-// Sum over the 64 lanes of a wavefront (fp32), result in every lane: DPP rotations inside each
+// Sum over aligned groups of L = 16, 32 or 64 lanes (fp32), result in every lane: DPP rotations inside each
 // 16-lane row, then the lane-swap instructions across rows.
 template <int kCtrl>
 __device__ __forceinline__ float dpp_f32(float v) {
@@ -27,80 +27,89 @@ __device__ __forceinline__ unsigned opaque_copy_u(unsigned x) {
     asm volatile("v_mov_b32 %0, %1" : "=v"(yv) : "v"(x));
     return yv;
 }
-__device__ __forceinline__ float wave_sum_f32(float v) {
+template <int L>
+__device__ __forceinline__ float lanes_sum_f32(float v) {
     v += dpp_f32<0x128>(v);                                    // row_ror:8
     v += dpp_f32<0x124>(v);                                    // row_ror:4
     v += dpp_f32<0x122>(v);                                    // row_ror:2
     v += dpp_f32<0x121>(v);                                    // row_ror:1
+    if (L == 16) return v;
     const unsigned u = __builtin_bit_cast(unsigned, v);
     const auto a = __builtin_amdgcn_permlane16_swap(u, opaque_copy_u(u), false, false);
     const unsigned a0 = a[0], a1 = a[1];
     v = __builtin_bit_cast(float, a0) + __builtin_bit_cast(float, a1);
+    if (L == 32) return v;
     const unsigned u2 = __builtin_bit_cast(unsigned, v);
     const auto b = __builtin_amdgcn_permlane32_swap(u2, opaque_copy_u(u2), false, false);
     const unsigned b0 = b[0], b1 = b[1];
     return __builtin_bit_cast(float, b0) + __builtin_bit_cast(float, b1);
 }
 
-constexpr int kLnChunks = 4;                                   // 16-byte chunks per lane: C <= 64 * 4 * 8 = 2048
-
-template <typename In>
+// A row is NC chunks of V consecutive values for each of L lanes, chunk i of lane l at (L i + l) V; a wavefront has 64 / L rows at
+// a time.  FULL: C == L V NC, every lane has all of them; otherwise chunks past C are not there.
+// Few rows are a chain of latencies (launch, row, two reductions, store); many are bound by memory, if a row costs little beside
+// its own bytes.  So gamma and beta, twice the bytes of a row, stay in registers while a group of lanes takes every stride-th row, the
+// next of which is on its way while it works on one; 16 lanes read and write whole cache lines; and narrow rows share the
+// divisions and the root of a wavefront.  With a wavefront to every row, eight values a chunk (of which a third of the lanes had
+// none at C = 768) and room for C = 2048 in every launch, us before and now: 25 216 x 768 16.1 and 14.1 (5.5 TB/s), 8850 x 768
+// 7.7 and 7.4, 25 216 x 384 11.5 and 8.9, 25 216 x 192 11.1 and 6.1, 1334 rows of either 3.9 and 3.7.
+constexpr int kLnWaves = 16384;                                // about twice what the chip holds at once (8850 x 1024: 8.1 us, with half of it 8.7)
+template <typename In, int L, int V, int NC, bool FULL>
 __global__ __launch_bounds__(kBlockThreads)
 void layernorm_kernel(const uint16_t* x, const uint16_t* __restrict__ gamma,          // y may be x: no restrict
                       const uint16_t* __restrict__ beta, uint16_t* y, int rows_cap,
-                      const int32_t* __restrict__ rows_dev, int C, float eps) {
+                      const int32_t* __restrict__ rows_dev, int C, float eps, int64_t stride) {
+    typedef LinearLine<V> Chunk;
     int rows = rows_cap;
     if (rows_dev) { const int r = *rows_dev; rows = r < rows ? r : rows; }
-    const int lane = threadIdx.x & (kWaveSize - 1);
-    const int row = blockIdx.x * (kBlockThreads / kWaveSize) + (threadIdx.x >> 6);
+    const int sub = threadIdx.x % L;
+    int64_t row = (int64_t)blockIdx.x * (kBlockThreads / L) + threadIdx.x / L;
     if (row >= rows) return;
-    const int chunks = C / 8;
-    const uint4* src = reinterpret_cast<const uint4*>(x + (int64_t)row * C);
-    // every load of the kernel is issued up front (the row, and the scale / shift vectors the last
-    // pass needs), so the two reductions run while gamma and beta are still on their way
-    uint4 raw_x[kLnChunks], raw_g[kLnChunks], raw_b[kLnChunks];
+    auto there = [&](int i) { return FULL || (sub + L * i) * V < C; };
+    auto load = [&](const uint16_t* src, Chunk (&c)[NC]) {
 #pragma unroll
-    for (int i = 0; i < kLnChunks; ++i) {
-        const int c = lane + kWaveSize * i;
-        if (c < chunks) {
-            raw_x[i] = src[c];
-            raw_g[i] = reinterpret_cast<const uint4*>(gamma)[c];
-            raw_b[i] = reinterpret_cast<const uint4*>(beta)[c];
+        for (int i = 0; i < NC; ++i)
+            if (there(i)) c[i] = reinterpret_cast<const Chunk*>(src)[sub + L * i];
+    };
+    // the first row and what the last pass needs are requested together
+    Chunk next[NC], g_raw[NC], b_raw[NC];
+    load(x + row * C, next);
+    load(gamma, g_raw);
+    load(beta, b_raw);
+    for (; row < rows; row += stride) {
+        float v[NC][V];
+        float sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            if (there(i)) {
+                next[i].unpack(In{}, v[i]);
+#pragma unroll
+                for (int e = 0; e < V; ++e) sum += v[i][e];
+            } else {
+#pragma unroll
+                for (int e = 0; e < V; ++e) v[i][e] = 0.f;
+            }
         }
-    }
-    float v[kLnChunks][8];
-    float sum = 0.f;
+        if (row + stride < rows) load(x + (row + stride) * C, next);
+        const float mean = lanes_sum_f32<L>(sum) / (float)C;
+        float sq = 0.f;
 #pragma unroll
-    for (int i = 0; i < kLnChunks; ++i) {
-        const int c = lane + kWaveSize * i;
-        if (c < chunks) {
-            unpack8(In{}, raw_x[i], v[i]);
+        for (int i = 0; i < NC; ++i)
+            if (there(i))
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sum += v[i][e];
-        } else {
+                for (int e = 0; e < V; ++e) { const float d = v[i][e] - mean; sq = __builtin_fmaf(d, d, sq); }
+        const float rstd = 1.0f / sqrtf(lanes_sum_f32<L>(sq) / (float)C + eps);
+        Chunk* dst = reinterpret_cast<Chunk*>(y + row * C);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[i][e] = 0.f;
-        }
-    }
-    const float mean = wave_sum_f32(sum) / (float)C;
-    float sq = 0.f;
+        for (int i = 0; i < NC; ++i) {
+            if (there(i)) {
+                float gm[V], bt[V], out[V];
+                g_raw[i].unpack(In{}, gm);
+                b_raw[i].unpack(In{}, bt);
 #pragma unroll
-    for (int i = 0; i < kLnChunks; ++i)
-        if (lane + kWaveSize * i < chunks)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) { const float d = v[i][e] - mean; sq = __builtin_fmaf(d, d, sq); }
-    const float rstd = 1.0f / sqrtf(wave_sum_f32(sq) / (float)C + eps);
-    uint4* dst = reinterpret_cast<uint4*>(y + (int64_t)row * C);
-#pragma unroll
-    for (int i = 0; i < kLnChunks; ++i) {
-        const int c = lane + kWaveSize * i;
-        if (c < chunks) {
-            float gm[8], bt[8], out[8];
-            unpack8(In{}, raw_g[i], gm);
-            unpack8(In{}, raw_b[i], bt);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) out[e] = __builtin_fmaf((v[i][e] - mean) * rstd, gm[e], bt[e]);
-            dst[c] = pack8(In{}, out);
+                for (int e = 0; e < V; ++e) out[e] = __builtin_fmaf((v[i][e] - mean) * rstd, gm[e], bt[e]);
+                dst[sub + L * i] = Chunk::pack(In{}, out);
+            }
         }
     }
 }
@@ -119,22 +128,30 @@ hipError_t launch_linear(const void* x, const void* w, const void* bias, const v
                             : launch_linear_bf16(c, g.groups, args, stream);
 }
 
-int layernorm_max_width() { return kWaveSize * kLnChunks * 8; }
+int layernorm_max_width() { return kWaveSize * 4 * 8; }
 
 hipError_t launch_layernorm(const void* x, const void* gamma, const void* beta, void* y, int rows_cap,
                             const int32_t* rows_dev, int C, float eps, ragged_dtype dt, hipStream_t stream) {
-    const int per = kBlockThreads / kWaveSize;
-    const dim3 grid((rows_cap + per - 1) / per), block(kBlockThreads);
-    const uint16_t* xp = static_cast<const uint16_t*>(x);
-    const uint16_t* gp = static_cast<const uint16_t*>(gamma);
-    const uint16_t* bp = static_cast<const uint16_t*>(beta);
-    uint16_t* yp = static_cast<uint16_t*>(y);
-    hipError_t err;
-    if (dt == RAGGED_F16)
-        err = launch_kernel((layernorm_kernel<F16>), grid, block, stream, xp, gp, bp, yp, rows_cap, rows_dev, C, eps);
-    else
-        err = launch_kernel((layernorm_kernel<BF16>), grid, block, stream, xp, gp, bp, yp, rows_cap, rows_dev, C, eps);
-    return err;
+    auto launch = [&](auto kernel, int lanes) {
+        // the same number of rows for every group of lanes (but for one), as few as the wavefronts that run at once allow
+        const int64_t at_once = (int64_t)kLnWaves * (kWaveSize / lanes), each = (rows_cap + at_once - 1) / at_once;
+        const int per = kBlockThreads / lanes, groups = (int)(((rows_cap + each - 1) / each + per - 1) / per);
+        return launch_kernel(kernel, dim3(groups), dim3(kBlockThreads), stream, static_cast<const uint16_t*>(x),
+                             static_cast<const uint16_t*>(gamma), static_cast<const uint16_t*>(beta), static_cast<uint16_t*>(y),
+                             rows_cap, rows_dev, C, eps, (int64_t)groups * per);
+    };
+    auto typed = [&](auto in) {
+        typedef decltype(in) In;
+        // widths of 8, 12 or 16 values for each of 16, 32 or 64 lanes fill whole wavefronts
+#define LN_FULL(L, V, NC) if (C == L * V * NC) return launch(layernorm_kernel<In, L, V, NC, true>, L);
+        LN_FULL(16, 8, 1) LN_FULL(16, 4, 3) LN_FULL(32, 8, 1) LN_FULL(32, 4, 3) LN_FULL(64, 8, 1) LN_FULL(64, 4, 3) LN_FULL(64, 8, 2)
+        LN_FULL(64, 2, 5) LN_FULL(64, 2, 7)
+#undef LN_FULL
+        if (C <= 512) return launch(layernorm_kernel<In, 64, 8, 1, false>, 64);
+        if (C <= 1024) return launch(layernorm_kernel<In, 64, 8, 2, false>, 64);
+        return launch(layernorm_kernel<In, 64, 8, 4, false>, 64);
+    };
+    return dt == RAGGED_F16 ? typed(F16{}) : typed(BF16{});
 }
 
 }  // namespace ragged
