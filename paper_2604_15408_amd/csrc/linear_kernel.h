@@ -268,7 +268,8 @@ void linear_kernel(const int32_t* rows_ptr, int rows_cap, int n_tiles, const uin
     // ---- residual: its first kAhead 16-row groups are requested with the first half of the last step but one (all of them where
     // there are registers for it)
     typedef LinearLine<NJ> Line;                               // NJ consecutive outputs of a row
-    constexpr int kMost = NJ < 8 ? MT : MT == 8 ? 2 : MT == 7 ? 4 : MT, kAhead = RES ? kMost : 1;
+    constexpr int kMost = NJ == 8 && MT == 8 ? 2 : NJ == 8 && MT == 7 ? 4 : NJ == 6 && MT * PER_CU == 8 ? 1 : MT;
+    constexpr int kAhead = RES ? kMost : 1;
     Line r_raw[kAhead][4];
     __amdgpu_buffer_rsrc_t r_rsrc = buf_rsrc(p.res, 0);
     const uint32_t out_row = (uint32_t)N * 2u;
@@ -488,6 +489,7 @@ hipError_t launch_linear_tile(const TileShape& shape, int groups, const LinearAr
 #define LINEAR_CASE(NJ, MT, PER_CU) \
     if (shape.nj == NJ && shape.mt == MT && shape.per_cu == PER_CU) LINEAR_LAUNCH(NJ, MT, PER_CU, false)
     LINEAR_SHAPES(LINEAR_CASE)
+    LINEAR_WIDE_PAIRS(LINEAR_CASE)
 #undef LINEAR_CASE
 #undef LINEAR_LAUNCH
     return hipErrorInvalidValue;

@@ -101,10 +101,12 @@ struct LinearCursor {
     }
 };
 
-// The tile shapes there are, as {NJ, MT, PER_CU}: 32 NJ features x 32 MT tokens, PER_CU work-groups on a CU.
+// The tile shapes there are, as {NJ, MT, PER_CU}: 32 NJ features x 32 MT tokens, PER_CU work-groups on a CU.  (Pairs of 192 x 128
+// fill the LDS of a CU exactly, with two stages each.)
 #define LINEAR_SHAPES(X) \
     X(8, 8, 1) X(8, 7, 1) X(8, 6, 1) X(8, 5, 1) X(8, 4, 1) X(6, 4, 1) X(6, 2, 1) X(4, 4, 1) X(4, 3, 1) X(2, 1, 1) \
     X(6, 3, 2) X(4, 4, 2) X(4, 2, 2) X(2, 4, 2) X(2, 2, 2)
+#define LINEAR_WIDE_PAIRS(X) X(6, 4, 2)
 
 // Tile shape.  The tiles are handed out evenly, n = ceil(tiles / 256) to a CU.  Where one work-group has a CU to itself they
 // follow each other,
@@ -113,29 +115,30 @@ struct LinearCursor {
 //     n / 2 * (k-steps * pair_step_ns + pair_tile_ns + GELU) + n % 2 * (k-steps * step_ns + tile_ns + GELU),
 // and the shape with the least of it is taken (rows: the caller's estimate, or the capacity).  Large tiles need the fewest
 // operand bytes per product and suit long contractions, small ones fill the chip when rows are few, the heights in between
-// are there because a round is paid whole (12 544 x 768 x 3072: 52 us in 237 tiles of 160 rows, 61 in 147 of 256), and two
-// groups of up to 192 x 96 suit short contractions and GELU, where the epilogue is a large part: 12 608 x 1536 x 384 with
-// GELU takes 31.4 us in tiles of 256 x 160, 27.2 in pairs of 128 x 128; 12 608 x 3072 x 768 with GELU 78.5 in 256 x 224, 69.9
-// in pairs of 192 x 96; 12 608 x 768 x 3072 52.9 in 256 x 160, 68 in pairs of 128 x 128.
-// The constants are a least-squares fit to 29 row counts from 20 to 50 432 at the four layers of 768-, 384- and 192-wide blocks
-// in both types (per shape; where it is within 40 % of the fastest); the shape taken is 0.5 % slower than the fastest of all
-// on average and 12 % at most.
+// are there because a round is paid whole (12 608 x 768 x 3072: 51 us in 237 tiles of 160 rows, 66 in 150 of 256), and two
+// groups of up to 192 x 128 suit short contractions and GELU, where the epilogue is a large part: 12 608 x 1536 x 384 with
+// GELU takes 30.4 us in 256 x 160, 25.6 in pairs of 128 x 128; 25 216 x 3072 x 768 with GELU 145 in 256 x 256, 125 in pairs of
+// 192 x 96, 119 in pairs of 192 x 128, which move a sixth fewer operand bytes through LDS (16 000 rows: 90, 82 and 78);
+// 12 608 x 768 x 3072 51 in 256 x 160, 66 in pairs of 128 x 128.
+// The constants are a least-squares fit to 32 row counts from 20 to 50 432 at the four layers of 768-, 384- and 192-wide blocks
+// (per shape; where it is within 40 % of the fastest; constants then moved by up to 3 % a step, 25 % a tile, towards fewer wrong
+// picks); the shape taken is 0.4 % slower than the fastest of all on average, 11 % at most (192-wide layers).
 constexpr int kCus = 256;
-constexpr int kGeluNs = 85, kPairGeluNs = 62;                  // per nj * mt of a tile, of a pair of tiles
+constexpr int kGeluNs = 118, kPairGeluNs = 102;               // per nj * mt of a tile, of a pair of tiles
 struct TileShape { int nj, mt, per_cu, step_ns, tile_ns, pair_step_ns, pair_tile_ns; };
 constexpr TileShape kTileShapes[] = {
-    {8, 8, 1, 1320, 6660, 0, 0}, {8, 7, 1, 1140, 6260, 0, 0}, {8, 6, 1, 1010, 5790, 0, 0}, {8, 5, 1, 880, 4470, 0, 0},
-    {8, 4, 1, 730, 3740, 0, 0}, {6, 4, 1, 600, 2650, 0, 0}, {6, 2, 1, 380, 1610, 0, 0}, {4, 4, 1, 425, 1890, 0, 0},
-    {4, 3, 1, 365, 1500, 0, 0}, {2, 1, 1, 150, 620, 0, 0},
-    {6, 3, 2, 530, 1600, 900, 3700}, {4, 4, 2, 490, 1100, 830, 3300}, {4, 2, 2, 290, 680, 545, 1630},
-    {2, 4, 2, 265, 890, 555, 1660}, {2, 2, 2, 190, 560, 340, 1070}};
+    {8, 8, 1, 1310, 6020, 0, 0}, {8, 7, 1, 1115, 5130, 0, 0}, {8, 6, 1, 970, 4800, 0, 0}, {8, 5, 1, 845, 4530, 0, 0},
+    {8, 4, 1, 725, 3670, 0, 0}, {6, 4, 1, 590, 1900, 0, 0}, {6, 2, 1, 370, 1140, 0, 0}, {4, 4, 1, 410, 1850, 0, 0},
+    {4, 3, 1, 365, 1180, 0, 0}, {2, 1, 1, 135, 520, 0, 0},
+    {6, 3, 2, 505, 770, 915, 2600}, {4, 4, 2, 485, 760, 805, 2650}, {4, 2, 2, 260, 500, 525, 1260},
+    {2, 4, 2, 250, 650, 535, 1640}, {2, 2, 2, 160, 500, 345, 740}, {6, 4, 2, 705, 1230, 1040, 4080}};
 // Outputs and residual are reached by 32-bit offsets from a tile's first row (256 rows of 2^22 features are 2^31 bytes); wider
 // rows have a form of the smallest tile with 64-bit addresses.
 inline bool linear_is_wide(int N) { return N > 1 << 22; }
 // rows: the caller's estimate, or the capacity
 inline TileShape pick_linear_shape(int rows, int N, int K, int act) {
     if (linear_is_wide(N)) return TileShape{2, 1, 1, 0, 0, 0, 0};
-    TileShape pick = kTileShapes[sizeof(kTileShapes) / sizeof(kTileShapes[0]) - 1];        // N is a multiple of 64: this one always fits
+    TileShape pick{};                                          // N is a multiple of 64: the 64-wide ones always fit
     int64_t best = INT64_MAX;
     for (const TileShape& c : kTileShapes) {
         if (N % (32 * c.nj) != 0) continue;
