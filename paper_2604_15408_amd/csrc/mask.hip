@@ -1,7 +1,7 @@
 // A keep-mask producer for the pipeline's first stage (Section 4.3 item 2 accepts any method that
 // yields a per-token keep mask; Section 5 prunes by a threshold on the l2 norm of the token features
 // at a fixed ratio without defining it further).  Two kernels:
-//   token_scores_l2_kernel: score[row] = sum_c x[row][c]^2.  One wavefront per row, fp64
+//   token_scores_l2_kernel: score[row] = sum_c x[row][c]^2.  8 to 64 lanes per row, fp64
 //     accumulation: a square of a 16-bit value is exact in fp64, so for ordinary data the score does
 //     not depend on the summation order and ranking decisions agree with any other exact evaluation.
 //   keep_topk_kernel: per image, token 0 (the class token) is kept and, of the others, the k-1 with
@@ -15,25 +15,40 @@ namespace {
 
 constexpr int kMaxMaskTokens = 1536;
 
-template <typename V8>
+// L lanes share a row, lane l holds its 16-byte chunks l, L + l, ... (NC of them, all requested before any is used; NC 0: as many
+// as there are, one after the other).  The kernel is bound by memory if enough of it is requested at once: with a whole wavefront
+// to every row and a loop over its chunks, a third or more of the lanes had nothing to ask for at C = 768, 384 and 192, and
+// every row paid six exchanges of 64-bit sums for itself.  fp16, operands from HBM, us before and now: 50 432 x 768 20.1 and 15.1
+// (5.1 TB/s), 50 432 x 384 13.2 and 8.5, 50 432 x 192 10.6 and 5.3, 12 608 x 768 6.2 and 5.3, 394 rows of either 2.8 and 2.8.
+// (With several rows to a group of lanes, the next on its way: the same up to 384, 50 432 x 768 15.7 to 16.8.)
+template <typename V8, int L, int NC>
 __global__ __launch_bounds__(kBlockThreads)
 void token_scores_l2_kernel(const uint4* __restrict__ x, int64_t rows, int chunks, double* __restrict__ scores) {
-    const int lane = threadIdx.x & (kWaveSize - 1);
-    const int64_t row = (int64_t)blockIdx.x * (kBlockThreads / kWaveSize) + (threadIdx.x >> 6);
+    const int sub = threadIdx.x % L;
+    const int64_t row = (int64_t)blockIdx.x * (kBlockThreads / L) + threadIdx.x / L;
     if (row >= rows) return;
-    const uint4* src = x + row * chunks;
+    const uint4* src = x + row * (NC > 0 ? L * NC : chunks);
     double acc = 0.0;
-    for (int c = lane; c < chunks; c += kWaveSize) {
-        const V8 v = as_vec8<V8>(src[c]);
+    auto add = [&](const uint4& raw) {
+        const V8 v = as_vec8<V8>(raw);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const double d = (double)(float)v[e];
             acc = __builtin_fma(d, d, acc);
         }
+    };
+    if (NC > 0) {
+        uint4 raw[NC > 0 ? NC : 1];
+#pragma unroll
+        for (int i = 0; i < NC; ++i) raw[i] = src[L * i + sub];
+#pragma unroll
+        for (int i = 0; i < NC; ++i) add(raw[i]);
+    } else {
+        for (int c = sub; c < chunks; c += L) add(src[c]);
     }
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, kWaveSize);
-    if (lane == 0) scores[row] = acc;
+    for (int off = L / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, kWaveSize);
+    if (sub == 0) scores[row] = acc;
 }
 
 // One work-group per (image, 32 tokens): eight lanes share a token and split the range of rivals
@@ -71,14 +86,20 @@ int keep_topk_max_tokens() { return kMaxMaskTokens; }
 
 hipError_t launch_token_scores_l2(const void* x, int64_t rows, int C, ragged_dtype dt, double* scores,
                                   hipStream_t stream) {
-    const int per = kBlockThreads / kWaveSize;
-    const dim3 grid((unsigned)((rows + per - 1) / per)), block(kBlockThreads);
-    hipError_t err;
-    if (dt == RAGGED_F16)
-        err = launch_kernel((token_scores_l2_kernel<f16x8>), grid, block, stream, static_cast<const uint4*>(x), rows, C / 8, scores);
-    else
-        err = launch_kernel((token_scores_l2_kernel<bf16x8>), grid, block, stream, static_cast<const uint4*>(x), rows, C / 8, scores);
-    return err;
+    auto launch = [&](auto kernel, int lanes) {
+        const int per = kBlockThreads / lanes;
+        return launch_kernel(kernel, dim3((unsigned)((rows + per - 1) / per)), dim3(kBlockThreads), stream,
+                             static_cast<const uint4*>(x), rows, C / 8, scores);
+    };
+    auto typed = [&](auto vec) {
+        typedef decltype(vec) V8;
+        // widths that 8 to 64 lanes share out in two or three chunks each
+#define SCORES_FULL(L, NC) if (C == 8 * L * NC) return launch(token_scores_l2_kernel<V8, L, NC>, L);
+        SCORES_FULL(8, 3) SCORES_FULL(16, 3) SCORES_FULL(32, 2) SCORES_FULL(32, 3) SCORES_FULL(64, 2)
+#undef SCORES_FULL
+        return launch(token_scores_l2_kernel<V8, 64, 0>, 64);
+    };
+    return dt == RAGGED_F16 ? typed(f16x8{}) : typed(bf16x8{});
 }
 
 hipError_t launch_keep_topk(const double* scores, int B, int N, int k, uint8_t* keep, hipStream_t stream) {
