@@ -15,6 +15,23 @@ __device__ __forceinline__ void wave_copy_row(const uint4* __restrict__ src, uin
     for (int u = lane; u < units; u += kWaveSize) dst[u] = src[u];
 }
 
+// The general forms of pack and zero-filling unpack move four rows of a wavefront at a time, all requested before the first is
+// written (rows of up to 1024 values; longer ones keep the loop, as four of them do not fit the registers).  One row at a time
+// its load waited for the store of the row before.  fp16, operands from HBM, us before and now: pack of 256 x 197 x 768 at keep
+// 0.5 / 0.9 22.9 and 21.0 / 33.7 and 30.8, 128 x 197 x 768 at 0.5 13.8 and 12.2, 50 x 333 x 1024 12.1 and 10.2; unpack of
+// 256 x 197 x 768 at 0.5 22.2 and 21.1, 64 x 577 x 768 dense 24.7 and 22.6, 256 x 577 x 192 24.6 and 20.3.
+// The rows have to be in registers here: the compiler otherwise moves each load down to the store of its row, and a wavefront
+// waits for one row (and for the stores in front of it) at a time.
+__device__ __forceinline__ void hold_rows(uint4 (&row)[4][2]) {
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        u32x4 v = __builtin_bit_cast(u32x4, row[r / 2][r % 2]);
+        asm volatile("" : "+v"(v));
+        row[r / 2][r % 2] = __builtin_bit_cast(uint4, v);
+    }
+}
+
 // ------------------------------------------------------------------------------------------------
 // pack: one work-group per (image i, chunk of `chunk` <= 64 consecutive tokens).
 //   P      = kept tokens before this chunk in the whole batch (flat mask prefix)  -> destination base
@@ -79,7 +96,9 @@ void pack_kernel(const uint4* __restrict__ x, const uint8_t* __restrict__ keep, 
         }
     }
 
-    const int P = prefix_finish(keep, prefix, lds4);           // kept tokens before this chunk in the batch
+    // kept tokens before this chunk in the batch.  (Masks beyond 16 KB: 24 KB a pass instead of 16, each of which is a round trip;
+    // 48 KB: the registers cost narrow rows up to 8 %.)
+    const int P = prefix_finish<EARLY ? kPrefixWords : 6>(keep, prefix, lds4);
 
     if (wave == 0) {
         if (mine) {
@@ -106,7 +125,35 @@ void pack_kernel(const uint4* __restrict__ x, const uint8_t* __restrict__ keep, 
         uint64_t rest = bits;
 #pragma unroll
         for (int z = 0; z < 3; ++z) rest = z < wave ? (rest & (rest - 1)) : rest;
-        for (int k = wave; rest != 0; k += 4) {                // one iteration per row of this wavefront
+        int k = wave;
+        if (units <= 2 * kWaveSize) {
+            // four rows at a time, requested before the first of them is written
+            while (k < in_chunk_count) {
+                uint4 row[4][2];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    row[r][0] = row[r][1] = make_uint4(0u, 0u, 0u, 0u);
+                    if (k + 4 * r < in_chunk_count) {
+                        const uint4* src = x + (int64_t)(row0 + __builtin_ctzll(rest)) * units;
+                        if (lane < units) row[r][0] = src[lane];
+                        if (lane + kWaveSize < units) row[r][1] = src[lane + kWaveSize];
+#pragma unroll
+                        for (int z = 0; z < 4; ++z) rest &= rest - 1;
+                    }
+                }
+                hold_rows(row);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int64_t dst = (int64_t)P + k + 4 * r;
+                    if (k + 4 * r >= in_chunk_count || dst >= cap_rows) break;
+                    if (lane < units) packed[dst * units + lane] = row[r][0];
+                    if (lane + kWaveSize < units) packed[dst * units + lane + kWaveSize] = row[r][1];
+                }
+                k += 16;
+            }
+            return;
+        }
+        for (; rest != 0; k += 4) {                            // one iteration per row of this wavefront
             const int t = __builtin_ctzll(rest);
             const int64_t dst = (int64_t)P + k;
             if (dst >= cap_rows) break;
@@ -178,6 +225,42 @@ void unpack_fill_kernel(const uint4* __restrict__ src, const uint8_t* __restrict
     const uint64_t bits = __ballot(mine);
 
     const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
+    if (units <= 2 * kWaveSize) {
+        // four rows at a time: the kept ones are requested, the dropped ones written while those arrive
+        for (int t0w = wave; t0w < live; t0w += 16) {
+            uint4 row[4][2];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                row[r][0] = row[r][1] = zero;
+                const int t = t0w + 4 * r;
+                if (t < live && ((bits >> t) & 1ull)) {
+                    const uint4* from = src + (base + __popcll(bits & ((1ull << t) - 1ull))) * units;
+                    if (lane < units) row[r][0] = from[lane];
+                    if (lane + kWaveSize < units) row[r][1] = from[lane + kWaveSize];
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int t = t0w + 4 * r;
+                uint4* dst = out + (int64_t)(row0 + t) * units;
+                if (t < live && !((bits >> t) & 1ull)) {
+                    if (lane < units) dst[lane] = zero;
+                    if (lane + kWaveSize < units) dst[lane + kWaveSize] = zero;
+                }
+            }
+            hold_rows(row);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int t = t0w + 4 * r;
+                uint4* dst = out + (int64_t)(row0 + t) * units;
+                if (t < live && ((bits >> t) & 1ull)) {
+                    if (lane < units) dst[lane] = row[r][0];
+                    if (lane + kWaveSize < units) dst[lane + kWaveSize] = row[r][1];
+                }
+            }
+        }
+        return;
+    }
     for (int t = wave; t < live; t += 4) {
         uint4* dst = out + (int64_t)(row0 + t) * units;
         if ((bits >> t) & 1ull) {

@@ -1,4 +1,5 @@
-"""Forms of the kernels around a pruning point at their edges: scores for every split of a row over lanes."""
+"""Forms of the kernels around a pruning point at their edges: scores for every split of a row over lanes, pack and zero-filling
+unpack with none to many rows per wavefront, rows that are held in registers and longer ones, and masks of several passes."""
 import pytest
 import torch
 
@@ -20,3 +21,35 @@ def test_scores_every_split(dtype, C):
         want = (x.double() ** 2).sum(2)
         assert torch.all((scores[:rows].cpu() - want).abs() <= C * 2.0 ** -53 * want)
         assert scores[rows].item() == -1.0
+
+
+@pytest.mark.parametrize("B,N,C,keep,spare", [
+    (2, 197, 768, 1.0, 0),          # every row kept
+    (1, 64, 1024, 0.5, 0),          # the longest rows held in registers
+    (3, 65, 1032, 0.7, 0),          # longer ones
+    (220, 197, 8, 0.6, 0),          # 43 KB of mask, chunks of 32 tokens
+    (300, 577, 64, 0.9, 0),         # 173 KB of mask, chunks of 64: more than four rows for a wavefront
+    (300, 577, 64, 0.02, 0),        # wavefronts without rows
+    (220, 197, 512, 1.0, -1000),    # fewer packed rows than kept ones
+])
+def test_pack_unpack_forms(B, N, C, keep, spare):
+    gen = torch.Generator().manual_seed(B + N + C)
+    x = torch.randint(-30000, 30000, (B, N, C), generator=gen, dtype=torch.int16)
+    mask = torch.rand(B, N, generator=gen) < keep
+    lens = mask.sum(1)
+    T = int(lens.sum())
+    cap = T + spare
+    xd, kd = x.view(torch.float16).to(DEV), mask.to(torch.uint8).to(DEV)
+    packed = torch.zeros(cap + 1, C, dtype=torch.int16, device=DEV).view(torch.float16)
+    cu, gidx = torch.zeros(B + 1, dtype=torch.int32, device=DEV), torch.full((cap + 1,), -1, dtype=torch.int32, device=DEV)
+    binding.ragged_pack(xd, kd, packed[:cap], cu, gidx[:cap])
+    flat = torch.nonzero(mask.flatten()).flatten()
+    want = x.reshape(B * N, C)[flat]
+    assert torch.equal(cu.cpu()[1:].long(), torch.cumsum(lens, 0)) and cu[0].item() == 0
+    assert torch.equal(packed.view(torch.int16).cpu()[:cap], want[:cap]) and not torch.any(packed.view(torch.int16)[cap])
+    assert torch.equal(gidx.cpu()[:cap].long(), flat[:cap]) and gidx[cap].item() == -1
+    if spare < 0:
+        return
+    out = torch.full((B, N, C), 77, dtype=torch.int16, device=DEV)
+    binding.ragged_unpack(packed[:cap], kd, cu, gidx[:cap], out.view(torch.float16), 1)
+    assert torch.equal(out.cpu(), torch.where(mask[:, :, None], x, torch.zeros_like(x)))
