@@ -6,7 +6,7 @@
 // file launches it in the shape that linear_walk.h picks and holds LayerNorm.
 //
 // layernorm_kernel: 16, 32 or 64 lanes per row, the row held in registers, two passes (mean, then the
-//   biased variance of the centred values) in fp32.
+//   biased variance of the centred values) in fp32, in an order that does not depend on the form.
 //
 // Rows: the caller passes a capacity and, optionally, a device pointer to the real row count (for
 // example &cu_seqlens[B]); work-groups past it exit, so nothing is read back to the host.
@@ -45,72 +45,108 @@ __device__ __forceinline__ float lanes_sum_f32(float v) {
     return __builtin_bit_cast(float, b0) + __builtin_bit_cast(float, b1);
 }
 
-// A row is NC chunks of V consecutive values for each of L lanes, chunk i of lane l at (L i + l) V; a wavefront has 64 / L rows at
-// a time.  FULL: C == L V NC, every lane has all of them; otherwise chunks past C are not there.
-// Few rows are a chain of latencies (launch, row, two reductions, store); many are bound by memory, if a row costs little beside
-// its own bytes.  So gamma and beta, twice the bytes of a row, stay in registers while a group of lanes takes every stride-th row, the
-// next of which is on its way while it works on one; 16 lanes read and write whole cache lines; and narrow rows share the
-// divisions and the root of a wavefront.  With a wavefront to every row, eight values a chunk (of which a third of the lanes had
-// none at C = 768) and room for C = 2048 in every launch, us before and now: 25 216 x 768 16.1 and 14.1 (5.5 TB/s), 8850 x 768
-// 7.7 and 7.4, 25 216 x 384 11.5 and 8.9, 25 216 x 192 11.1 and 6.1, 1334 rows of either 3.9 and 3.7.
-constexpr int kLnWaves = 16384;                                // about twice what the chip holds at once (8850 x 1024: 8.1 us, with half of it 8.7)
-template <typename In, int L, int V, int NC, bool FULL>
+// Value e of a chunk plus a, rounded once.  fp16: one mixed-precision fma with `one` = 1, which the compiler must not see as a
+// constant (it would make a conversion and a sum of it again).
+__device__ __forceinline__ float plus_value(F16, const LinearLine<8>& c, int e, float a, float one) {
+    return __builtin_fmaf((float)__builtin_bit_cast(_Float16, (uint16_t)(c.w[e / 2] >> 16 * (e % 2))), one, a);
+}
+__device__ __forceinline__ float plus_value(BF16, const LinearLine<8>& c, int e, float a, float) {
+    return __builtin_bit_cast(float, e % 2 ? c.w[e / 2] & 0xffff0000u : c.w[e / 2] << 16) + a;
+}
+
+// L lanes have a row, NC chunks of eight consecutive values each: chunk i of lane l is the row's chunk L i + l, and C > 8 L (NC - 1),
+// so that only a lane's last chunk may be missing.
+// Every form adds up in the same order, so that a row's bits do not depend on how many rows there are: that of 64 lanes with
+// chunks l, l + 64, ..., one partial sum a lane, then pairs of lanes 8, 4, 2, 1, 16 and 32 apart.  A lane that stands for
+// several of the 64 has a partial sum for each (part).
+// Few rows are a chain of latencies (launch, row, two reductions, store), shortest with the row spread over many lanes.  Many are
+// bound by memory if a row costs few instructions: no idle lanes in a wavefront, several rows sharing the divisions and the
+// root, fp16 values converted by the fma that uses them, and buffer loads and stores, which need no branch for a chunk or a row that is
+// not there.  Beyond kLnWaves wavefronts a lane takes every stride-th row, and gamma and beta stay for all of them.
+// us, operands from HBM, one wavefront and four chunks a lane to every row / now: 25 216 x 768 fp16 19.1 / 16.3, bf16 19.3 / 16.2;
+// 8850 x 768 9.0 / 7.7; 25 216 x 384 14.7 / 10.7; 25 216 x 192 11.3 / 6.3; 12 608 x 1000 14.2 / 12.5; 12 608 x 2048 23.0 / 21.5;
+// 394 rows of 768, 384, 192: 2.49, 2.25, 2.23 / 2.21, 2.06, 2.05.
+constexpr int kLnWaves = 32768;                                // about four times what the chip holds: 50 432 x 768 31.2 us with half of it, 29.3 now
+constexpr int kLnFewRows = 2048;                               // more lanes a row up to here: 394 / 1334 / 2600 rows of 768 2.2 / 2.9 / 3.8 us, fewer 2.4 / 2.8 / 3.8;
+                                                               // of 384 2.06 / 2.3 / 2.9 and 2.33 / 2.5 / 2.7
+template <typename In, int L, int NC>
 __global__ __launch_bounds__(kBlockThreads)
 void layernorm_kernel(const uint16_t* x, const uint16_t* __restrict__ gamma,          // y may be x: no restrict
                       const uint16_t* __restrict__ beta, uint16_t* y, int rows_cap,
                       const int32_t* __restrict__ rows_dev, int C, float eps, int64_t stride) {
-    typedef LinearLine<V> Chunk;
-    int rows = rows_cap;
-    if (rows_dev) { const int r = *rows_dev; rows = r < rows ? r : rows; }
-    const int sub = threadIdx.x % L;
-    int64_t row = (int64_t)blockIdx.x * (kBlockThreads / L) + threadIdx.x / L;
+    typedef LinearLine<8> Chunk;
+    constexpr int kRows = kWaveSize / L;                       // rows of a wavefront at a time
+    constexpr int kParts = kRows < NC ? kRows : NC;
+    static_assert(kParts <= 3, "of four partial sums the second pair would be added up first");
+    int given = rows_cap;
+    if (rows_dev) { const int r = *rows_dev; given = r < given ? r : given; }
+    const int rows = __builtin_amdgcn_readfirstlane(given);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & (kWaveSize - 1), sub = lane % L;
+    int64_t row = ((int64_t)blockIdx.x * (kBlockThreads / kWaveSize) + wave) * kRows;
     if (row >= rows) return;
-    auto there = [&](int i) { return FULL || (sub + L * i) * V < C; };
-    auto load = [&](const uint16_t* src, Chunk (&c)[NC]) {
+    const uint32_t row_bytes = (uint32_t)C * 2u;
+    const bool last = 8 * (sub + L * (NC - 1)) < C;            // this lane has a last chunk
+    // of chunk i, `first` bytes behind its buffer's start; a chunk that is not there lies outside of every buffer
+    auto offset = [&](int i, uint32_t first) -> uint32_t { return i < NC - 1 || last ? first + 16u * (sub + L * i) : 1u << 31; };
+    auto records = [&]() -> uint32_t { return (uint32_t)(rows - row < kRows ? rows - row : kRows) * row_bytes; };
+    const uint32_t lane_row = lane / L * row_bytes;
+    auto load = [&](__amdgpu_buffer_rsrc_t rsrc, uint32_t first, Chunk (&c)[NC]) {
 #pragma unroll
-        for (int i = 0; i < NC; ++i)
-            if (there(i)) c[i] = reinterpret_cast<const Chunk*>(src)[sub + L * i];
+        for (int i = 0; i < NC; ++i) c[i] = Chunk::load(rsrc, offset(i, first));
     };
     // the first row and what the last pass needs are requested together
     Chunk next[NC], g_raw[NC], b_raw[NC];
-    load(x + row * C, next);
-    load(gamma, g_raw);
-    load(beta, b_raw);
-    for (; row < rows; row += stride) {
-        float v[NC][V];
-        float sum = 0.f;
+    load(buf_rsrc(x + row * C, records()), lane_row, next);
+    load(buf_rsrc(gamma, row_bytes), 0, g_raw);
+    load(buf_rsrc(beta, row_bytes), 0, b_raw);
+    float one = 1.0f;
+    asm("" : "+s"(one));
+    while (true) {
+        const __amdgpu_buffer_rsrc_t y_rsrc = buf_rsrc(y + row * C, records());
+        Chunk cur[NC];
+        float v[NC][8], part[kParts] = {};
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            if (there(i)) {
-                next[i].unpack(In{}, v[i]);
+            cur[i] = next[i];
 #pragma unroll
-                for (int e = 0; e < V; ++e) sum += v[i][e];
-            } else {
-#pragma unroll
-                for (int e = 0; e < V; ++e) v[i][e] = 0.f;
-            }
+            for (int e = 0; e < 8; ++e) part[i % kParts] = plus_value(In{}, cur[i], e, part[i % kParts], one);
         }
-        if (row + stride < rows) load(x + (row + stride) * C, next);
-        const float mean = lanes_sum_f32<L>(sum) / (float)C;
-        float sq = 0.f;
+        row += stride;
+        const bool more = row < rows;
+        if (more) load(buf_rsrc(x + row * C, records()), lane_row, next);
+        auto total = [&]() {
+            float t = lanes_sum_f32<L>(part[0]);
 #pragma unroll
-        for (int i = 0; i < NC; ++i)
-            if (there(i))
+            for (int i = 1; i < kParts; ++i) t += lanes_sum_f32<L>(part[i]);
+            return t;
+        };
+        const float mean = total() / (float)C;
 #pragma unroll
-                for (int e = 0; e < V; ++e) { const float d = v[i][e] - mean; sq = __builtin_fmaf(d, d, sq); }
-        const float rstd = 1.0f / sqrtf(lanes_sum_f32<L>(sq) / (float)C + eps);
-        Chunk* dst = reinterpret_cast<Chunk*>(y + row * C);
+        for (int i = 0; i < kParts; ++i) part[i] = 0.f;
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            if (there(i)) {
-                float gm[V], bt[V], out[V];
-                g_raw[i].unpack(In{}, gm);
-                b_raw[i].unpack(In{}, bt);
+            const float centre = i < NC - 1 || last ? -mean : 0.f;
 #pragma unroll
-                for (int e = 0; e < V; ++e) out[e] = __builtin_fmaf((v[i][e] - mean) * rstd, gm[e], bt[e]);
-                dst[sub + L * i] = Chunk::pack(In{}, out);
+            for (int e = 0; e < 8; ++e) {
+                v[i][e] = plus_value(In{}, cur[i], e, centre, one);
+                part[i % kParts] = __builtin_fmaf(v[i][e], v[i][e], part[i % kParts]);
             }
         }
+        const float rstd = 1.0f / sqrtf(total() / (float)C + eps);
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            float gm[8], bt[8], out[8];
+            // (they stay as they are: converted in front of the loop they would fill twice the registers)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(g_raw[i].w[k]), "+v"(b_raw[i].w[k]));
+            g_raw[i].unpack(In{}, gm);
+            b_raw[i].unpack(In{}, bt);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) out[e] = __builtin_fmaf(v[i][e] * rstd, gm[e], bt[e]);
+            Chunk::pack(In{}, out).store(y_rsrc, offset(i, lane_row));
+        }
+        if (!more) return;
     }
 }
 
@@ -133,7 +169,7 @@ int layernorm_max_width() { return kWaveSize * 4 * 8; }
 hipError_t launch_layernorm(const void* x, const void* gamma, const void* beta, void* y, int rows_cap,
                             const int32_t* rows_dev, int C, float eps, ragged_dtype dt, hipStream_t stream) {
     auto launch = [&](auto kernel, int lanes) {
-        // the same number of rows for every group of lanes (but for one), as few as the wavefronts that run at once allow
+        // the same number of rows for every group of lanes (but for one), as few as kLnWaves wavefronts allow
         const int64_t at_once = (int64_t)kLnWaves * (kWaveSize / lanes), each = (rows_cap + at_once - 1) / at_once;
         const int per = kBlockThreads / lanes, groups = (int)(((rows_cap + each - 1) / each + per - 1) / per);
         return launch_kernel(kernel, dim3(groups), dim3(kBlockThreads), stream, static_cast<const uint16_t*>(x),
@@ -142,14 +178,16 @@ hipError_t launch_layernorm(const void* x, const void* gamma, const void* beta, 
     };
     auto typed = [&](auto in) {
         typedef decltype(in) In;
-        // widths of 8, 12 or 16 values for each of 16, 32 or 64 lanes fill whole wavefronts
-#define LN_FULL(L, V, NC) if (C == L * V * NC) return launch(layernorm_kernel<In, L, V, NC, true>, L);
-        LN_FULL(16, 8, 1) LN_FULL(16, 4, 3) LN_FULL(32, 8, 1) LN_FULL(32, 4, 3) LN_FULL(64, 8, 1) LN_FULL(64, 4, 3) LN_FULL(64, 8, 2)
-        LN_FULL(64, 2, 5) LN_FULL(64, 2, 7)
-#undef LN_FULL
-        if (C <= 512) return launch(layernorm_kernel<In, 64, 8, 1, false>, 64);
-        if (C <= 1024) return launch(layernorm_kernel<In, 64, 8, 2, false>, 64);
-        return launch(layernorm_kernel<In, 64, 8, 4, false>, 64);
+#define LN_FORM(L, NC) if (C <= 8 * L * NC) return launch(layernorm_kernel<In, L, NC>, L);
+        LN_FORM(16, 1)
+        if (rows_cap <= kLnFewRows) {
+            LN_FORM(32, 1) LN_FORM(64, 1)
+        } else {
+            LN_FORM(16, 2) LN_FORM(16, 3) LN_FORM(32, 2) LN_FORM(32, 3)
+        }
+        LN_FORM(64, 2) LN_FORM(64, 3)
+        return launch(layernorm_kernel<In, 64, 4>, 64);
+#undef LN_FORM
     };
     return dt == RAGGED_F16 ? typed(F16{}) : typed(BF16{});
 }
