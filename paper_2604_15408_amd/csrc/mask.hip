@@ -15,21 +15,24 @@ namespace {
 
 constexpr int kMaxMaskTokens = 1536;
 
-// L lanes share a row, lane l holds its 16-byte chunks l, L + l, ... (NC of them, all requested before any is used; NC 0: as many
-// as there are, one after the other).  The kernel is bound by memory if enough of it is requested at once: with a whole wavefront
-// to every row and a loop over its chunks, a third or more of the lanes had nothing to ask for at C = 768, 384 and 192, and
-// every row paid six exchanges of 64-bit sums for itself.  fp16, operands from HBM, us before and now: 50 432 x 768 20.1 and 15.1
-// (5.1 TB/s), 50 432 x 384 13.2 and 8.5, 50 432 x 192 10.6 and 5.3, 12 608 x 768 6.2 and 5.3, 394 rows of either 2.8 and 2.8.
-// (With several rows to a group of lanes, the next on its way: the same up to 384, 50 432 x 768 15.7 to 16.8.)
+// L lanes share a row, lane l holds its 16-byte chunks l, L + l, ... (NC <= 3 of them, the last may be missing, all requested before
+// any is used; NC 0: as many as there are, one after the other).  The kernel is bound by memory if enough of it is requested at
+// once: with a whole wavefront to every row and a loop over its chunks, a third or more of the lanes had nothing to ask for at
+// C = 768, 384 and 192, and every row paid six exchanges of 64-bit sums for itself.  So L is the smallest that covers the row in
+// three chunks.  fp16, operands from HBM, us with a wavefront to every row and now: 50 432 x 768 18.7 and 14.2 (5.5 TB/s), x 640 17.5
+// and 12.1, x 384 12.6 and 8.2, x 192 9.9 and 4.9, x 64 9.6 and 3.1, 12 608 x 768 5.5 and 4.6, x 1536 8.8 and 7.8, 394 rows of any 2.0
+// and 2.0.  (With several rows to a group of lanes, the next on its way: the same up to 384, 50 432 x 768 15.7 to 16.8.)
+// The sums are formed in one order for every L, that of a wavefront with chunks l, 64 + l, ... on lane l, so that scores (and
+// ties) do not depend on the form: a lane that stands for several of the 64 has a partial sum for each, added up in the order of
+// the exchanges 32, 16, 8 that it does without.
 template <typename V8, int L, int NC>
 __global__ __launch_bounds__(kBlockThreads)
 void token_scores_l2_kernel(const uint4* __restrict__ x, int64_t rows, int chunks, double* __restrict__ scores) {
     const int sub = threadIdx.x % L;
     const int64_t row = (int64_t)blockIdx.x * (kBlockThreads / L) + threadIdx.x / L;
     if (row >= rows) return;
-    const uint4* src = x + row * (NC > 0 ? L * NC : chunks);
-    double acc = 0.0;
-    auto add = [&](const uint4& raw) {
+    const uint4* src = x + row * chunks;
+    auto add = [&](const uint4& raw, double& acc) {
         const V8 v = as_vec8<V8>(raw);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -37,15 +40,22 @@ void token_scores_l2_kernel(const uint4* __restrict__ x, int64_t rows, int chunk
             acc = __builtin_fma(d, d, acc);
         }
     };
+    constexpr int kParts = NC == 0 || L == kWaveSize ? 1 : kWaveSize / L < NC ? kWaveSize / L : NC;
+    double part[3] = {0.0, 0.0, 0.0};
     if (NC > 0) {
         uint4 raw[NC > 0 ? NC : 1];
+        const bool last = sub + L * (NC - 1) < chunks;
 #pragma unroll
-        for (int i = 0; i < NC; ++i) raw[i] = src[L * i + sub];
+        for (int i = 0; i < NC; ++i) raw[i] = src[i < NC - 1 || last ? L * i + sub : 0];
+        if (!last) raw[NC > 0 ? NC - 1 : 0] = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-        for (int i = 0; i < NC; ++i) add(raw[i]);
+        for (int i = 0; i < NC; ++i) add(raw[i], part[i % kParts]);
     } else {
-        for (int c = sub; c < chunks; c += L) add(src[c]);
+        for (int c = sub; c < chunks; c += L) add(src[c], part[0]);
     }
+    double acc = part[0];
+    if (kParts == 3) acc += part[2];
+    if (kParts >= 2) acc += part[1];
 #pragma unroll
     for (int off = L / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, kWaveSize);
     if (sub == 0) scores[row] = acc;
@@ -93,10 +103,11 @@ hipError_t launch_token_scores_l2(const void* x, int64_t rows, int C, ragged_dty
     };
     auto typed = [&](auto vec) {
         typedef decltype(vec) V8;
-        // widths that 8 to 64 lanes share out in two or three chunks each
-#define SCORES_FULL(L, NC) if (C == 8 * L * NC) return launch(token_scores_l2_kernel<V8, L, NC>, L);
-        SCORES_FULL(8, 3) SCORES_FULL(16, 3) SCORES_FULL(32, 2) SCORES_FULL(32, 3) SCORES_FULL(64, 2)
-#undef SCORES_FULL
+        const int chunks = C / 8;
+#define SCORES_FORM(L, NC) if (chunks <= L * NC) return launch(token_scores_l2_kernel<V8, L, NC>, L);
+        SCORES_FORM(8, 1) SCORES_FORM(8, 2) SCORES_FORM(8, 3) SCORES_FORM(16, 2) SCORES_FORM(16, 3)
+        SCORES_FORM(32, 2) SCORES_FORM(32, 3) SCORES_FORM(64, 2) SCORES_FORM(64, 3)
+#undef SCORES_FORM
         return launch(token_scores_l2_kernel<V8, 64, 0>, 64);
     };
     return dt == RAGGED_F16 ? typed(f16x8{}) : typed(bf16x8{});

@@ -10,7 +10,10 @@ DEV = "cuda:0"
 _TD = {"f16": torch.float16, "bf16": torch.bfloat16}
 
 
-@pytest.mark.parametrize("C", [8, 192, 384, 512, 640, 768, 1024, 1032])
+_WIDTHS = [8, 64, 72, 128, 192, 200, 384, 392, 512, 640, 768, 776, 1024, 1032, 1536, 1544]
+
+
+@pytest.mark.parametrize("C", _WIDTHS)
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_scores_every_split(dtype, C):
     """fp64 sums of exact squares: any order is within C roundings of the true sum."""
@@ -21,6 +24,26 @@ def test_scores_every_split(dtype, C):
         want = (x.double() ** 2).sum(2)
         assert torch.all((scores[:rows].cpu() - want).abs() <= C * 2.0 ** -53 * want)
         assert scores[rows].item() == -1.0
+
+
+@pytest.mark.parametrize("C", _WIDTHS)
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_scores_order_of_sums(dtype, C):
+    """The bits are those of 64 lanes with chunks l, l + 64, ... of eight values on lane l and exchanges 32, 16, ... 1 apart, whatever
+    the split, for values over so many binades that every sum is rounded (a square is exact in fp64)."""
+    gen = torch.Generator().manual_seed(C)
+    wide = {"f16": 10, "bf16": 30}[dtype]
+    x = (torch.randn(65, C, generator=gen) * torch.exp2(torch.randint(-wide, wide, (65, C), generator=gen))).to(_TD[dtype])
+    x[x.isinf()] = 1.0
+    square = x.double() ** 2
+    lane = torch.zeros(65, 64, dtype=torch.float64)
+    for k in range(C):
+        lane[:, k // 8 % 64] += square[:, k]
+    for half in (32, 16, 8, 4, 2, 1):
+        lane = lane[:, :half] + lane[:, half:]
+    scores = torch.zeros(65, 1, dtype=torch.float64, device=DEV)
+    binding.ragged_token_scores_l2(x[:, None, :].to(DEV), scores)
+    assert torch.equal(scores.cpu(), lane)
 
 
 @pytest.mark.parametrize("B,N,C,keep,spare", [
