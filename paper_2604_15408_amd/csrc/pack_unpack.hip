@@ -128,12 +128,14 @@ void pack_kernel(const uint4* __restrict__ x, const uint8_t* __restrict__ keep, 
         int k = wave;
         if (units <= 2 * kWaveSize) {
             // four rows at a time, requested before the first of them is written
-            while (k < in_chunk_count) {
+            const int64_t room = cap_rows - P;                 // rows that the output has room for
+            const int n = room < in_chunk_count ? (int)room : in_chunk_count;
+            for (; k < n; k += 16) {
                 uint4 row[4][2];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     row[r][0] = row[r][1] = make_uint4(0u, 0u, 0u, 0u);
-                    if (k + 4 * r < in_chunk_count) {
+                    if (k + 4 * r < n) {
                         const uint4* src = x + (int64_t)(row0 + __builtin_ctzll(rest)) * units;
                         if (lane < units) row[r][0] = src[lane];
                         if (lane + kWaveSize < units) row[r][1] = src[lane + kWaveSize];
@@ -144,12 +146,11 @@ void pack_kernel(const uint4* __restrict__ x, const uint8_t* __restrict__ keep, 
                 hold_rows(row);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int64_t dst = (int64_t)P + k + 4 * r;
-                    if (k + 4 * r >= in_chunk_count || dst >= cap_rows) break;
-                    if (lane < units) packed[dst * units + lane] = row[r][0];
-                    if (lane + kWaveSize < units) packed[dst * units + lane + kWaveSize] = row[r][1];
+                    if (k + 4 * r >= n) break;
+                    uint4* dst = packed + ((int64_t)P + k + 4 * r) * units;
+                    if (lane < units) dst[lane] = row[r][0];
+                    if (lane + kWaveSize < units) dst[lane + kWaveSize] = row[r][1];
                 }
-                k += 16;
             }
             return;
         }
