@@ -93,8 +93,7 @@ __device__ __forceinline__ int count_word(uint4 v) {
 }
 
 // This thread's share of the count: the words and bytes requested by prefix_issue() plus, for ranges beyond
-// 16 KB, the rest of the body, kMore words per thread and pass.
-template <int kMore = kPrefixWords>
+// 16 KB, the rest of the body.
 __device__ inline int prefix_count_thread(const uint8_t* __restrict__ base, const PrefixLoads& p) {
     const int tid = threadIdx.x;
     const int tail0 = p.head + (p.body << 4);
@@ -105,13 +104,13 @@ __device__ inline int prefix_count_thread(const uint8_t* __restrict__ base, cons
         count += count_word(p.w[j]);
     }
     const uint4* words = reinterpret_cast<const uint4*>(base + p.head);
-    for (int w0 = tid + kPrefixWords * kBlockThreads; w0 < p.body; w0 += kMore * kBlockThreads) {
-        uint4 more[kMore];                                     // all loads of a pass issued before any is used
+    for (int w0 = tid + kPrefixWords * kBlockThreads; w0 < p.body; w0 += kPrefixWords * kBlockThreads) {
+        uint4 more[kPrefixWords];                             // all loads of a pass issued before any is used
 #pragma unroll
-        for (int j = 0; j < kMore; ++j)
+        for (int j = 0; j < kPrefixWords; ++j)
             more[j] = w0 + j * kBlockThreads < p.body ? words[w0 + j * kBlockThreads] : make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-        for (int j = 0; j < kMore; ++j) count += count_word(more[j]);
+        for (int j = 0; j < kPrefixWords; ++j) count += count_word(more[j]);
     }
     return count;
 }
@@ -125,9 +124,8 @@ __device__ __forceinline__ void prefix_post(int thread_count, int* lds4) {
 }
 __device__ __forceinline__ int prefix_total(const int* lds4) { return lds4[0] + lds4[1] + lds4[2] + lds4[3]; }
 
-template <int kMore = kPrefixWords>
 __device__ inline int prefix_finish(const uint8_t* __restrict__ base, const PrefixLoads& p, int* lds4) {
-    prefix_post(prefix_count_thread<kMore>(base, p), lds4);
+    prefix_post(prefix_count_thread(base, p), lds4);
     __syncthreads();
     return prefix_total(lds4);
 }

@@ -96,9 +96,8 @@ void pack_kernel(const uint4* __restrict__ x, const uint8_t* __restrict__ keep, 
         }
     }
 
-    // kept tokens before this chunk in the batch.  (Masks beyond 16 KB: 24 KB a pass instead of 16, each of which is a round trip;
-    // 48 KB: the registers cost narrow rows up to 8 %.)
-    const int P = prefix_finish<EARLY ? kPrefixWords : 6>(keep, prefix, lds4);
+    // kept tokens before this chunk in the batch (masks beyond 16 KB in passes of 16 KB; of 24: the registers cost 1 to 5 %)
+    const int P = prefix_finish(keep, prefix, lds4);
 
     if (wave == 0) {
         if (mine) {
