@@ -15,22 +15,28 @@ __device__ __forceinline__ void wave_copy_row(const uint4* __restrict__ src, uin
     for (int u = lane; u < units; u += kWaveSize) dst[u] = src[u];
 }
 
-// The general forms of pack and zero-filling unpack move four rows of a wavefront at a time, all requested before the first is
-// written (rows of up to 1024 values; longer ones keep the loop, as four of them do not fit the registers).  One row at a time
-// its load waited for the store of the row before.  fp16, operands from HBM, us before and now: pack of 256 x 197 x 768 at keep
-// 0.5 / 0.9 22.9 and 21.0 / 33.7 and 30.8, 128 x 197 x 768 at 0.5 13.8 and 12.2, 50 x 333 x 1024 12.1 and 10.2; unpack of
-// 256 x 197 x 768 at 0.5 22.2 and 21.1, 64 x 577 x 768 dense 24.7 and 22.6, 256 x 577 x 192 24.6 and 20.3.
+// The general forms of pack and zero-filling unpack move R rows of a wavefront at a time, all requested before the first is written,
+// of W 16-byte words a lane (rows beyond 128 words: W = 0, one by one, as several do not fit the registers).  One row at a time its
+// load waits for the store of the row before.  R is 4, and 2 in the smallest chunks, where a wavefront has at most four (pack) or
+// two (unpack) rows and longer code costs what it saves (pack of 128 x 197 x 192 at keep 0.1, us one by one / 2 / 4 at a time: 5.1 /
+// 5.1 / 5.3, at 0.8 8.0 / 7.4 / 7.4).  fp16, operands from HBM, us one by one and now: pack of 256 x 197 x 768 at keep 0.5 / 0.9
+// 22.9 and 21.0 / 33.7 and 30.8, 128 x 197 x 768 at 0.5 13.8 and 12.2, 50 x 333 x 1024 12.1 and 10.2; unpack of 256 x 197 x 768 at 0.5
+// 22.2 and 21.1, 64 x 577 x 768 dense 24.7 and 22.6, 256 x 577 x 192 24.6 and 20.3, 64 x 197 x 192 at 0.8 5.0 and 4.6.
+// It is slower in one place, unpack of long rows nearly all kept with 9 to 20 MB to write: 32 x 197 x 1024 at keep 0.1 / 0.5 / 0.8
+// / 1 8 % and 6 % faster / 6 % and 8 % slower.
 // The rows have to be in registers here: the compiler otherwise moves each load down to the store of its row, and a wavefront
 // waits for one row (and for the stores in front of it) at a time.
-__device__ __forceinline__ void hold_rows(uint4 (&row)[4][2]) {
+template <int R, int W>
+__device__ __forceinline__ void hold_rows(uint4 (&row)[R][W]) {
     typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        u32x4 v = __builtin_bit_cast(u32x4, row[r / 2][r % 2]);
+    for (int r = 0; r < R * W; ++r) {
+        u32x4 v = __builtin_bit_cast(u32x4, row[r / W][r % W]);
         asm volatile("" : "+v"(v));
-        row[r / 2][r % 2] = __builtin_bit_cast(uint4, v);
+        row[r / W][r % W] = __builtin_bit_cast(uint4, v);
     }
 }
+constexpr int words_held(int units) { return units > 2 * kWaveSize ? 0 : units > kWaveSize ? 2 : 1; }          // W for rows of that many words
 
 // ------------------------------------------------------------------------------------------------
 // pack: one work-group per (image i, chunk of `chunk` <= 64 consecutive tokens).
@@ -40,7 +46,7 @@ __device__ __forceinline__ void hold_rows(uint4 (&row)[4][2]) {
 // ------------------------------------------------------------------------------------------------
 constexpr int kMaxEarly = 4;    // rows a wavefront may hold in registers (EARLY needs chunk <= 16)
 
-template <bool EARLY>
+template <bool EARLY, int W, int R>
 __global__ __launch_bounds__(kBlockThreads)
 void pack_kernel(const uint4* __restrict__ x, const uint8_t* __restrict__ keep, int N, int units,
                  uint4* __restrict__ packed, int64_t cap_rows, int32_t* __restrict__ cu_seqlens,
@@ -125,30 +131,33 @@ void pack_kernel(const uint4* __restrict__ x, const uint8_t* __restrict__ keep, 
 #pragma unroll
         for (int z = 0; z < 3; ++z) rest = z < wave ? (rest & (rest - 1)) : rest;
         int k = wave;
-        if (units <= 2 * kWaveSize) {
-            // four rows at a time, requested before the first of them is written
+        if (W > 0) {
+            // R rows at a time, requested before the first of them is written
             const int64_t room = cap_rows - P;                 // rows that the output has room for
             const int n = room < in_chunk_count ? (int)room : in_chunk_count;
-            for (; k < n; k += 16) {
-                uint4 row[4][2];
+            for (; k < n; k += 4 * R) {
+                uint4 row[R][W > 0 ? W : 1];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    row[r][0] = row[r][1] = make_uint4(0u, 0u, 0u, 0u);
+                for (int r = 0; r < R; ++r) {
+#pragma unroll
+                    for (int w = 0; w < W; ++w) row[r][w] = make_uint4(0u, 0u, 0u, 0u);
                     if (k + 4 * r < n) {
                         const uint4* src = x + (int64_t)(row0 + __builtin_ctzll(rest)) * units;
-                        if (lane < units) row[r][0] = src[lane];
-                        if (lane + kWaveSize < units) row[r][1] = src[lane + kWaveSize];
+#pragma unroll
+                        for (int w = 0; w < W; ++w)
+                            if (lane + w * kWaveSize < units) row[r][w] = src[lane + w * kWaveSize];
 #pragma unroll
                         for (int z = 0; z < 4; ++z) rest &= rest - 1;
                     }
                 }
                 hold_rows(row);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
+                for (int r = 0; r < R; ++r) {
                     if (k + 4 * r >= n) break;
                     uint4* dst = packed + ((int64_t)P + k + 4 * r) * units;
-                    if (lane < units) dst[lane] = row[r][0];
-                    if (lane + kWaveSize < units) dst[lane + kWaveSize] = row[r][1];
+#pragma unroll
+                    for (int w = 0; w < W; ++w)
+                        if (lane + w * kWaveSize < units) dst[lane + w * kWaveSize] = row[r][w];
                 }
             }
             return;
@@ -193,6 +202,7 @@ void unpack_scatter_kernel(const uint4* __restrict__ src, const int32_t* __restr
 // unpack, fill_mode 1: one work-group per (image, chunk) as in pack.  Kept tokens receive their
 // packed row (cu_seqlens[i] + rank inside the image); dropped tokens are written with +0 words.
 // ------------------------------------------------------------------------------------------------
+template <int W, int R>
 __global__ __launch_bounds__(kBlockThreads)
 void unpack_fill_kernel(const uint4* __restrict__ src, const uint8_t* __restrict__ keep,
                         const int32_t* __restrict__ cu_seqlens, int N, int units,
@@ -225,38 +235,40 @@ void unpack_fill_kernel(const uint4* __restrict__ src, const uint8_t* __restrict
     const uint64_t bits = __ballot(mine);
 
     const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
-    if (units <= 2 * kWaveSize) {
-        // four rows at a time: the kept ones are requested, the dropped ones written while those arrive
-        for (int t0w = wave; t0w < live; t0w += 16) {
-            uint4 row[4][2];
+    if (W > 0) {
+        // R rows at a time: the kept ones are requested, the dropped ones written while those arrive
+        for (int t0w = wave; t0w < live; t0w += 4 * R) {
+            uint4 row[R][W > 0 ? W : 1];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                row[r][0] = row[r][1] = zero;
+            for (int r = 0; r < R; ++r) {
                 const int t = t0w + 4 * r;
+#pragma unroll
+                for (int w = 0; w < W; ++w) row[r][w] = zero;
                 if (t < live && ((bits >> t) & 1ull)) {
                     const uint4* from = src + (base + __popcll(bits & ((1ull << t) - 1ull))) * units;
-                    if (lane < units) row[r][0] = from[lane];
-                    if (lane + kWaveSize < units) row[r][1] = from[lane + kWaveSize];
+#pragma unroll
+                    for (int w = 0; w < W; ++w)
+                        if (lane + w * kWaveSize < units) row[r][w] = from[lane + w * kWaveSize];
                 }
             }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            for (int r = 0; r < R; ++r) {
                 const int t = t0w + 4 * r;
                 uint4* dst = out + (int64_t)(row0 + t) * units;
-                if (t < live && !((bits >> t) & 1ull)) {
-                    if (lane < units) dst[lane] = zero;
-                    if (lane + kWaveSize < units) dst[lane + kWaveSize] = zero;
-                }
+                if (t < live && !((bits >> t) & 1ull))
+#pragma unroll
+                    for (int w = 0; w < W; ++w)
+                        if (lane + w * kWaveSize < units) dst[lane + w * kWaveSize] = zero;
             }
             hold_rows(row);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            for (int r = 0; r < R; ++r) {
                 const int t = t0w + 4 * r;
                 uint4* dst = out + (int64_t)(row0 + t) * units;
-                if (t < live && ((bits >> t) & 1ull)) {
-                    if (lane < units) dst[lane] = row[r][0];
-                    if (lane + kWaveSize < units) dst[lane + kWaveSize] = row[r][1];
-                }
+                if (t < live && ((bits >> t) & 1ull))
+#pragma unroll
+                    for (int w = 0; w < W; ++w)
+                        if (lane + w * kWaveSize < units) dst[lane + w * kWaveSize] = row[r][w];
             }
         }
         return;
@@ -348,8 +360,11 @@ hipError_t launch_pack(const void* x, const uint8_t* keep, int B, int N, int C, 
     // the early-load variant keeps the first 16 KB of mask prefix in registers; beyond that the
     // remaining prefix loads would queue behind the row loads, so larger masks take the plain order
     const bool early = chunk <= 4 * kMaxEarly && C / 8 <= 2 * kWaveSize && (int64_t)B * N <= 16384;
-    const hipError_t err = launch_kernel(early ? pack_kernel<true> : pack_kernel<false>, dim3(B * cpi),
-                       dim3(kBlockThreads), stream, static_cast<const uint4*>(x), keep, N, C / 8,
+    const int words = words_held(C / 8);
+    const auto kernel = early ? pack_kernel<true, 0, 1> : words == 0 ? pack_kernel<false, 0, 1> :
+                        chunk <= 16 ? (words == 1 ? pack_kernel<false, 1, 2> : pack_kernel<false, 2, 2>) :
+                                      (words == 1 ? pack_kernel<false, 1, 4> : pack_kernel<false, 2, 4>);
+    const hipError_t err = launch_kernel(kernel, dim3(B * cpi), dim3(kBlockThreads), stream, static_cast<const uint4*>(x), keep, N, C / 8,
                        static_cast<uint4*>(packed), cap_rows, cu_seqlens, gather_idx, chunk, cpi,
                        div_magic((uint32_t)cpi));
     return err;
@@ -368,7 +383,11 @@ hipError_t launch_unpack(const void* src, const uint8_t* keep, const int32_t* cu
     } else {
         const int chunk = pick_chunk(B, N, kUnpackFillMaxGroups);
         const int cpi = (N + chunk - 1) / chunk;
-        err = launch_kernel(unpack_fill_kernel, dim3(B * cpi), dim3(kBlockThreads), stream,
+        const int words = words_held(C / 8);
+        const auto kernel = words == 0 ? unpack_fill_kernel<0, 1> :
+                            chunk <= 8 ? (words == 1 ? unpack_fill_kernel<1, 2> : unpack_fill_kernel<2, 2>) :
+                                         (words == 1 ? unpack_fill_kernel<1, 4> : unpack_fill_kernel<2, 4>);
+        err = launch_kernel(kernel, dim3(B * cpi), dim3(kBlockThreads), stream,
                            static_cast<const uint4*>(src), keep, cu_seqlens, N, C / 8,
                            static_cast<uint4*>(out), chunk, cpi, div_magic((uint32_t)cpi));
     }

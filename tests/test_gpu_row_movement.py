@@ -46,14 +46,27 @@ def test_scores_order_of_sums(dtype, C):
     assert torch.equal(scores.cpu(), lane)
 
 
+# Pack takes rows of up to 1024 values ahead of its prefix count if the mask has at most 16 KB (and its chunks, then, 8 tokens).  Beyond
+# that its chunks have 16 tokens, over 32 768 tokens 32, over 65 536 64; those of the unpack have half as many.
 @pytest.mark.parametrize("B,N,C,keep,spare", [
     (2, 197, 768, 1.0, 0),          # every row kept
-    (1, 64, 1024, 0.5, 0),          # the longest rows held in registers
-    (3, 65, 1032, 0.7, 0),          # longer ones
-    (220, 197, 8, 0.6, 0),          # 43 KB of mask, chunks of 32 tokens
+    (1, 64, 1024, 0.5, 0),          # the longest rows ahead of the count
+    (3, 65, 1032, 0.7, 0),          # longer ones, one by one
+    (90, 197, 768, 0.5, 0),         # two words a lane in the smallest chunks
+    (30, 577, 1024, 1.0, 0),        # the longest of those, every row kept
+    (90, 197, 520, 0.05, 0),        # the shortest, hardly any kept
+    (256, 197, 768, 0.6, 0),        # chunks of 32 and 16: several passes over two words a lane
+    (120, 577, 776, 0.9, 0),        # chunks of 64 and 32
+    (90, 197, 512, 0.5, 0),         # one word a lane in the smallest chunks
+    (90, 197, 192, 1.0, 0),
+    (220, 197, 8, 0.6, 0),          # 43 KB of mask, chunks of 32 and 16: one word a lane
+    (220, 197, 512, 1.0, 0),
     (300, 577, 64, 0.9, 0),         # 173 KB of mask, chunks of 64: more than four rows for a wavefront
     (300, 577, 64, 0.02, 0),        # wavefronts without rows
     (220, 197, 512, 1.0, -1000),    # fewer packed rows than kept ones
+    (90, 197, 1024, 0.8, -3001),
+    (256, 197, 768, 0.7, -30002),
+    (30, 577, 1032, 1.0, -4003),
 ])
 def test_pack_unpack_forms(B, N, C, keep, spare):
     gen = torch.Generator().manual_seed(B + N + C)
