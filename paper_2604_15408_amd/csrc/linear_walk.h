@@ -132,16 +132,17 @@ constexpr TileShape kTileShapes[] = {
     {4, 3, 1, 365, 1180, 0, 0}, {2, 1, 1, 135, 520, 0, 0},
     {6, 3, 2, 505, 770, 915, 2600}, {4, 4, 2, 485, 760, 805, 2650}, {4, 2, 2, 260, 500, 525, 1260},
     {2, 4, 2, 250, 650, 535, 1640}, {2, 2, 2, 160, 500, 345, 740}, {6, 4, 2, 705, 1230, 1040, 4080}};
-// Outputs and residual are reached by 32-bit offsets from a tile's first row (256 rows of 2^22 features are 2^31 bytes); wider
-// rows have a form of the smallest tile with 64-bit addresses.
-inline bool linear_is_wide(int N) { return N > 1 << 22; }
+// Outputs and residual are reached by 32-bit offsets from a tile's first row, so that a tile's rows together may have up to 2^32
+// bytes: 256 rows below 2^23 features, 32 rows below 2^26.  Wider rows have a form of the smallest tile with 64-bit addresses.
+inline bool linear_offsets_fit(int mt, int N) { return (int64_t)(32 * mt) * N * 2 < (int64_t)1 << 32; }
+inline bool linear_is_wide(int N) { return !linear_offsets_fit(1, N); }
 // rows: the caller's estimate, or the capacity
 inline TileShape pick_linear_shape(int rows, int N, int K, int act) {
     if (linear_is_wide(N)) return TileShape{2, 1, 1, 0, 0, 0, 0};
-    TileShape pick{};                                          // N is a multiple of 64: the 64-wide ones always fit
+    TileShape pick{};                                          // N is a multiple of 64: the 64 x 32 one always fits
     int64_t best = INT64_MAX;
     for (const TileShape& c : kTileShapes) {
-        if (N % (32 * c.nj) != 0) continue;
+        if (N % (32 * c.nj) != 0 || !linear_offsets_fit(c.mt, N)) continue;
         const int64_t tiles = (int64_t)((rows + 32 * c.mt - 1) / (32 * c.mt)) * (N / (32 * c.nj));
         const int64_t n = (tiles + kCus - 1) / kCus, pairs = c.per_cu == 2 ? n / 2 : 0;
         const int ksteps = K / kTK, gelu = act == 1 ? c.nj * c.mt : 0;
@@ -154,11 +155,14 @@ inline TileShape pick_linear_shape(int rows, int N, int K, int act) {
 // Feature tiles per panel: the 32 CUs of an XCD then work on a patch of about 6 x 5 tiles, which pulls fewest operand
 // bytes into its L2 (12 544 x 3072 x 768: 78 -> 72.5 us against whole rows of tiles; widths of 4 to 6 are alike).
 constexpr int kPanel = 6;
+// tile_of() passes the panels one by one, so there are not too many of them (up to 24 576 features this changes nothing; 64 rows x
+// 151 936 x 768 62 us without the limit and 42 with it, 3 x 4 194 560 x 64 22 ms and 0.37; 1000 x 128 256 x 768 203 and 211 us).
+constexpr int kMaxPanels = 64;
 struct LinearGrid {
     int n_tiles, panel, last, groups;                          // last: width of the last panel
     LinearGrid(int nj, int mt, int per_cu, int rows_cap, int N) {
         n_tiles = N / (32 * nj);
-        const int panels = (n_tiles + kPanel - 1) / kPanel;
+        const int wanted = (n_tiles + kPanel - 1) / kPanel, panels = wanted < kMaxPanels ? wanted : kMaxPanels;
         panel = (n_tiles + panels - 1) / panels;
         last = n_tiles - (n_tiles - 1) / panel * panel;
         const int64_t tiles = (int64_t)((rows_cap + 32 * mt - 1) / (32 * mt)) * n_tiles;

@@ -1,6 +1,6 @@
-"""ragged_linear with rows of millions of features, where the 32-bit offsets of outputs and residual come to their end (2^22
-features: 256 rows are 2^31 bytes) and the form with 64-bit addresses begins.  Reference: the same in fp32 on the GPU, a
-stretch of features at a time, with the bound that test_gpu_block.py derives."""
+"""ragged_linear with rows of millions of features, where the 32-bit offsets of outputs and residual come to their end (a tile's rows
+together have up to 2^32 bytes: 256 rows below 2^23 features, 32 below 2^26) and the form with 64-bit addresses begins.  Reference:
+the same in fp32 on the GPU, a stretch of features at a time, with the bound that test_gpu_block.py derives."""
 import pytest
 import torch
 
@@ -12,7 +12,11 @@ DEV = "cuda:0"
 
 @pytest.mark.parametrize("rows,N,dtype,act,residual", [(257, 1 << 22, "f16", "none", True), (3, 1 << 22, "bf16", "gelu", False),
                                                        (3, (1 << 22) + 64, "f16", "gelu", True),
-                                                       (65, (1 << 22) + 64, "bf16", "none", False)])
+                                                       (65, (1 << 22) + 64, "bf16", "none", False),
+                                                       (257, (1 << 23) - 256, "f16", "none", True),
+                                                       (257, (1 << 23) + 256, "bf16", "none", True),
+                                                       (33, (1 << 26) - 64, "bf16", "none", False),
+                                                       (2, 1 << 26, "f16", "gelu", True), (33, 1 << 26, "bf16", "none", False)])
 def test_linear_wide_rows(rows, N, dtype, act, residual):
     K = 64
     tdt, ulp = {"f16": (torch.float16, 2.0 ** -10), "bf16": (torch.bfloat16, 2.0 ** -7)}[dtype]

@@ -31,6 +31,23 @@ def test_every_load_stays_inside_its_operand(shape):
     follow(shape, 0, tn * 3, 768, cap=tm)
 
 
+def test_wide_outputs():
+    """Tiles whose rows together have 2^32 bytes or more of output are not taken, all smaller ones are open; and with more panels
+    than the walk passes one by one, every tile is still taken once."""
+    taken = set()
+    for N in (1 << 22, (1 << 22) + 768, (1 << 23) - 768, 1 << 23, 1 << 24, 1 << 25, (1 << 26) - 64):
+        for rows in (1, 33, 100, 500, 2000):
+            for K in (64, 1024):
+                (nj, mt, per_cu), _ = rule.pick(rows, rows, N, K, "none")
+                assert 32 * mt * N * 2 < 1 << 32, (N, rows, K, mt)
+                taken.add((N, mt))
+    assert max(mt for N, mt in taken if 1 << 22 < N < 1 << 23) == 8
+    assert max(mt for N, mt in taken if N == 1 << 23) in (4, 5, 6, 7)
+    assert rule.pick(500, 500, 1 << 26, 1024, "none")[0] == (2, 1, 1)
+    for shape in rule.SHAPES:
+        follow(shape, 32 * shape[1] + 1, 32 * shape[0] * 1999, 64)
+
+
 @pytest.mark.parametrize("shape", rule.SHAPES)
 def test_a_negative_device_row_count_is_no_work(shape):
     """The number of tiles of such a count must not wrap round to a positive one."""
