@@ -489,7 +489,6 @@ hipError_t launch_linear_tile(const TileShape& shape, int groups, const LinearAr
 #define LINEAR_CASE(NJ, MT, PER_CU) \
     if (shape.nj == NJ && shape.mt == MT && shape.per_cu == PER_CU) LINEAR_LAUNCH(NJ, MT, PER_CU, false)
     LINEAR_SHAPES(LINEAR_CASE)
-    LINEAR_WIDE_PAIRS(LINEAR_CASE)
 #undef LINEAR_CASE
 #undef LINEAR_LAUNCH
     return hipErrorInvalidValue;

@@ -105,8 +105,7 @@ struct LinearCursor {
 // fill the LDS of a CU exactly, with two stages each.)
 #define LINEAR_SHAPES(X) \
     X(8, 8, 1) X(8, 7, 1) X(8, 6, 1) X(8, 5, 1) X(8, 4, 1) X(6, 4, 1) X(6, 2, 1) X(4, 4, 1) X(4, 3, 1) X(2, 1, 1) \
-    X(6, 3, 2) X(4, 4, 2) X(4, 2, 2) X(2, 4, 2) X(2, 2, 2)
-#define LINEAR_WIDE_PAIRS(X) X(6, 4, 2)
+    X(6, 4, 2) X(6, 3, 2) X(4, 4, 2) X(4, 2, 2) X(2, 4, 2) X(2, 2, 2)
 
 // Tile shape.  The tiles are handed out evenly, n = ceil(tiles / 256) to a CU.  Where one work-group has a CU to itself they
 // follow each other,
@@ -130,8 +129,8 @@ constexpr TileShape kTileShapes[] = {
     {8, 8, 1, 1310, 6020, 0, 0}, {8, 7, 1, 1115, 5130, 0, 0}, {8, 6, 1, 970, 4800, 0, 0}, {8, 5, 1, 845, 4530, 0, 0},
     {8, 4, 1, 725, 3670, 0, 0}, {6, 4, 1, 590, 1900, 0, 0}, {6, 2, 1, 370, 1140, 0, 0}, {4, 4, 1, 410, 1850, 0, 0},
     {4, 3, 1, 365, 1180, 0, 0}, {2, 1, 1, 135, 520, 0, 0},
-    {6, 3, 2, 505, 770, 915, 2600}, {4, 4, 2, 485, 760, 805, 2650}, {4, 2, 2, 260, 500, 525, 1260},
-    {2, 4, 2, 250, 650, 535, 1640}, {2, 2, 2, 160, 500, 345, 740}, {6, 4, 2, 705, 1230, 1040, 4080}};
+    {6, 4, 2, 705, 1230, 1040, 4080}, {6, 3, 2, 505, 770, 915, 2600}, {4, 4, 2, 485, 760, 805, 2650}, {4, 2, 2, 260, 500, 525, 1260},
+    {2, 4, 2, 250, 650, 535, 1640}, {2, 2, 2, 160, 500, 345, 740}};
 // Outputs and residual are reached by 32-bit offsets from a tile's first row, so that a tile's rows together may have up to 2^32
 // bytes: 256 rows below 2^23 features, 32 rows below 2^26.  Wider rows have a form of the smallest tile with 64-bit addresses.
 inline bool linear_offsets_fit(int mt, int N) { return (int64_t)(32 * mt) * N * 2 < (int64_t)1 << 32; }

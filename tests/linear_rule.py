@@ -21,7 +21,7 @@ def lib() -> ctypes.CDLL:
 
 # tiles of 32 nj features x 32 mt rows, per_cu work-groups on a CU
 SHAPES = [(8, 8, 1), (8, 7, 1), (8, 6, 1), (8, 5, 1), (8, 4, 1), (6, 4, 1), (6, 2, 1), (4, 4, 1), (4, 3, 1), (2, 1, 1),
-          (6, 3, 2), (4, 4, 2), (4, 2, 2), (2, 4, 2), (2, 2, 2)]
+          (6, 4, 2), (6, 3, 2), (4, 4, 2), (4, 2, 2), (2, 4, 2), (2, 2, 2)]
 
 
 @functools.lru_cache(None)
@@ -32,6 +32,16 @@ def stages():
     for i in range(lib().linear_shape_count()):
         lib().linear_shape(i, out)
         res[tuple(out[:3])] = out[3]
+    return res
+
+
+def table():
+    """The shapes that the rule chooses from, in its order."""
+    out = (ctypes.c_int * 3)()
+    res = []
+    for i in range(lib().linear_table_size()):
+        lib().linear_table_shape(i, out)
+        res.append(tuple(out))
     return res
 
 

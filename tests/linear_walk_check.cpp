@@ -100,6 +100,14 @@ void linear_shape(int i, int* out) {
 #undef CASE
 }
 
+// The table that the rule chooses from
+int linear_table_size(void) { return (int)(sizeof(kTileShapes) / sizeof(kTileShapes[0])); }
+void linear_table_shape(int i, int* out) {
+    out[0] = kTileShapes[i].nj;
+    out[1] = kTileShapes[i].mt;
+    out[2] = kTileShapes[i].per_cu;
+}
+
 // {nj, mt, per_cu, tiles of a call over `rows` rows} of the shape that the rule picks
 void linear_pick(int rows_hint, int rows, int N, int K, int act, int* out) {
     const TileShape c = pick_linear_shape(rows_hint, N, K, act);

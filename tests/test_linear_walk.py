@@ -14,7 +14,9 @@ def follow(shape, rows, N, K, cap=None):
 
 
 def test_shapes_are_the_library_s():
+    """Of the list that the kernels come from and of the rule's table."""
     assert list(rule.stages()) == rule.SHAPES
+    assert rule.table() == rule.SHAPES
 
 
 @pytest.mark.parametrize("shape", rule.SHAPES)
