@@ -1,8 +1,7 @@
-// What the linear layers and LayerNorm share: GELU and the conversion of 8 consecutive values of a row (internal).
+// GELU as the linear layers apply it to what they have summed up (internal).
 #pragma once
 
 #include "common.h"
-#include "mfma_lds.h"
 
 namespace ragged {
 
@@ -32,30 +31,6 @@ __device__ __forceinline__ float gelu_erf(float t) {
     p = __builtin_fmaf(p, a, -1.1511178016662598f);
     p = __builtin_fmaf(p, a, -1.0f);
     return __builtin_fmaf(-a, __builtin_amdgcn_exp2f(p), __builtin_elementwise_maximum(t, 0.f));
-}
-
-// Eight consecutive values of one row <-> 16 bytes.
-__device__ __forceinline__ void unpack8(F16, const uint4& a, float (&v)[8]) {
-    const f16x8 h = as_vec8<f16x8>(a);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = (float)h[e];
-}
-__device__ __forceinline__ void unpack8(BF16, const uint4& a, float (&v)[8]) {
-    const bf16x8 h = as_vec8<bf16x8>(a);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = (float)h[e];
-}
-__device__ __forceinline__ uint4 pack8(F16, const float (&v)[8]) {
-    f16x8 h;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) h[e] = (_Float16)v[e];
-    return __builtin_bit_cast(uint4, h);
-}
-__device__ __forceinline__ uint4 pack8(BF16, const float (&v)[8]) {
-    bf16x8 h;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) h[e] = (__bf16)v[e];
-    return __builtin_bit_cast(uint4, h);
 }
 
 }  // namespace ragged
