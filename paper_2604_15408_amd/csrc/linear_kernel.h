@@ -14,14 +14,15 @@
 //
 // A work-group has four wavefronts, one on each SIMD of a CU, each owning 16 NJ features x 16 MT tokens.  With a CU to itself
 // (PER_CU 1) a wavefront has the whole register file and holds up to 128 x 128 accumulators, and LDS traffic per product is
-// half of that of eight wavefronts of 64 x 128, which kept the LDS pipe busy as long as the matrix core (25 216 rows, us
-// before and now: 2304 x 768 102 and 86, 768 x 3072 144 and 102).  Its epilogue runs beside nothing, though.  With PER_CU 2 two
-// groups of up to 192 x 96 share the CU and one's epilogue runs beside the other's products, which is the faster form where
-// the contraction is short or the epilogue has GELU (12 608 x 1536 x 384 with GELU 31.7 -> 27.2, 25 216 x 3072 x 768 with GELU
-// 145 -> 130); linear_walk.h has the rule.  By the counters (fp16, us and share of the cycles with the matrix core busy):
-// 25 216 x 3072 x 768 without GELU 116 and 0.47, 12 608 x 768 x 3072 52 and 0.48, where a loop of products alone on this chip
-// sustains 0.50 to 0.56 of its rate; few rows are bound by the time of a step (LDS round trip, barrier) and by launch and
-// first loads (1334 x 768 x 3072 14 and 0.13, waiting 38 % of the time).
+// half of that of eight wavefronts of 64 x 128, which kept the LDS pipe busy as long as the matrix core (25 216 rows, us of
+// eight and of four when they took their place: 2304 x 768 102 and 86, 768 x 3072 144 and 102).  Its epilogue runs beside nothing,
+// though.  With PER_CU 2 two groups of up to 192 x 128 share the CU and one's epilogue runs beside the other's products, which is the
+// faster form where the contraction is short or the epilogue has GELU (12 608 x 1536 x 384 with GELU 30.4 us alone and 25.6 in
+// pairs, 25 216 x 3072 x 768 with GELU 145 and 119); linear_walk.h has the rule.  By the counters (fp16, no GELU, us and share of
+// the cycles with the matrix core busy): 25 216 x 3072 x 768 in 256 x 256 106 and 0.53, 12 608 x 2304 x 768 in pairs of 192 x 128 43 and
+// 0.45, 12 608 x 768 x 3072 49 and 0.51, where a loop of products alone on this chip sustains 0.50 to 0.56 of its rate; few
+// rows are bound by the time of a step (LDS round trip, barrier) and by launch and first loads (1334 x 768 x 3072 13.5 and
+// 0.13, waiting 37 % of the time).
 //
 // With a single wavefront on a SIMD nothing else fills the gap an instruction leaves, so the loop is laid out by issue slots:
 // one instruction between two MFMAs is free, a second independent VALU too, anything more (or an address computed in front of
@@ -37,7 +38,7 @@
 // A step is two halves of 32 k; fragments of the next half are read while the products of this one run:
 //   * more than two stages: one barrier per step, between the halves.  The ring is refilled half a step at a time (w with
 //     the first half, x with the second);
-//   * two stages (256 x 192 and more, and the pairs of 192 x 96 and 128 x 128): x of both halves is held a step ahead, which
+//   * two stages (256 x 192 and more, and the pairs of 192 x 128, 192 x 96 and 128 x 128): x of both halves is held a step ahead, which
 //     frees the x part of a stage at the start of its step and the w part in the middle, so that its loads spread over the
 //     whole step as well (issued in one half they queue up: 4 x 16 KB at 64 bytes a cycle).
 // The tiles of a work-group follow each other without a break: the last steps of one load the first of the next.

@@ -121,7 +121,9 @@ struct LinearCursor {
 // 12 608 x 768 x 3072 51 in 256 x 160, 66 in pairs of 128 x 128.
 // The constants are a least-squares fit to 32 row counts from 20 to 50 432 at the four layers of 768-, 384- and 192-wide blocks
 // (per shape; where it is within 40 % of the fastest; constants then moved by up to 3 % a step, 25 % a tile, towards fewer wrong
-// picks); the shape taken is 0.4 % slower than the fastest of all on average, 11 % at most (192-wide layers).
+// picks); the shape taken is 0.4 % slower than the fastest of all on average, 11 % at most (192-wide layers).  Where the capacity
+// stands for the rows and few of them are real, the tiles are too large (2521 rows of 25 216 x 384 x 384 6.8 us; with them as
+// the estimate 3.9).
 constexpr int kCus = 256;
 constexpr int kGeluNs = 118, kPairGeluNs = 102;               // per nj * mt of a tile, of a pair of tiles
 struct TileShape { int nj, mt, per_cu, step_ns, tile_ns, pair_step_ns, pair_tile_ns; };
