@@ -1,14 +1,23 @@
 """ragged_layernorm in every form of its kernel: 16, 32 and 64 lanes a row, widths that fill them and widths that do not, with so many
 rows that a lane takes several (one of them the last), fewer rows than the capacity, in place.  Bound: fp32 statistics (relative
 1e-6) and one rounding to the output type, as in test_gpu_block.py; and, bit for bit, the one order of summation that all forms have."""
+import re
+
 import numpy as np
 import pytest
 import torch
 
 from paper_2604_15408_amd import binding
+from paper_2604_15408_amd.build import CSRC
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
+
+
+def _constant(name):
+    return int(re.search(rf"constexpr int {name} = (\d+);", (CSRC / "linear.hip").read_text()).group(1))
+
+
 _TYPES = {"f16": (torch.float16, 2.0 ** -10), "bf16": (torch.bfloat16, 2.0 ** -7)}
 
 
@@ -16,11 +25,12 @@ _TYPES = {"f16": (torch.float16, 2.0 ** -10), "bf16": (torch.bfloat16, 2.0 ** -7
 @pytest.mark.parametrize("C", [8, 128, 192, 256, 384, 504, 512, 640, 768, 896, 1000, 1024, 1032, 2048])
 def test_layernorm_forms(C, dtype):
     tdt, ulp = _TYPES[dtype]
-    lanes = 16 if C <= 384 else 32 if C <= 768 else 64
-    at_once = 32768 * 64 // lanes
+    lanes = 16 if C <= 384 else 32 if C <= 768 else 64         # (of the form for many rows)
+    at_once = _constant("kLnWaves") * 64 // lanes
+    few = _constant("kLnFewRows")
     gen = torch.Generator(device=DEV).manual_seed(C)
     g, b = torch.randn(2, C, generator=gen, device=DEV).to(tdt)
-    for cap, rows in ((at_once + 5, at_once + 3), (2 * at_once + 1, at_once + at_once // 2), (2049, 2047), (33, 33), (65, 1)):
+    for cap, rows in ((at_once + 5, at_once + 3), (2 * at_once + 1, at_once + at_once // 2), (few + 1, few - 1), (few, few), (33, 33), (65, 1)):
         x = (torch.randn(cap, C, generator=gen, device=DEV) * 2 + 0.75).to(tdt)
         y = x.clone()
         binding.ragged_layernorm(y, g, b, y, torch.tensor([rows], dtype=torch.int32, device=DEV), 1e-6)
@@ -67,7 +77,7 @@ def test_layernorm_order_of_sums(C, dtype):
     x = (torch.randn(n, C, generator=gen) * 2 + 0.75).to(tdt)
     g, b = torch.randn(2, C, generator=gen).to(tdt)
     want = _in_order(x.float(), g.float(), b.float(), 1e-6).to(tdt)
-    for cap in (n, 2049):
+    for cap in (n, _constant("kLnFewRows") + 1):
         xd = torch.zeros(cap, C, dtype=tdt, device=DEV)
         xd[cap - n:] = x.to(DEV)
         y = torch.zeros_like(xd)
