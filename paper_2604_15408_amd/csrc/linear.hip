@@ -67,8 +67,10 @@ __device__ __forceinline__ float plus_value(BF16, const LinearLine<8>& c, int e,
 // 8850 x 768 9.0 / 7.7; 25 216 x 384 14.7 / 10.7; 25 216 x 192 11.3 / 6.3; 12 608 x 1000 14.2 / 12.5; 12 608 x 2048 23.0 / 21.5;
 // 394 rows of 768, 384, 192: 2.49, 2.25, 2.23 / 2.21, 2.06, 2.05.
 constexpr int kLnWaves = 32768;                                // about four times what the chip holds: 50 432 x 768 31.2 us with half of it, 29.3 now
-constexpr int kLnFewRows = 2048;                               // more lanes a row up to here: 394 / 1334 / 2600 rows of 768 2.2 / 2.9 / 3.8 us, fewer 2.4 / 2.8 / 3.8;
-                                                               // of 384 2.06 / 2.3 / 2.9 and 2.33 / 2.5 / 2.7
+// More lanes a row up to this capacity.  It is the row count that decides, but only the device knows it: with room for 4000 rows, of
+// which 10 / 33 / 100 % are there, bf16, many lanes take 2.25 / 2.93 / 4.40 us and few 2.48 / 2.77 / 4.37 at 768, 2.06 / 2.33 / 3.34 and
+// 2.42 / 2.56 / 3.12 at 384; over 10 to 100 % many win by 1 to 4 % up to room for 5000 and few by as much from 8000 on.
+constexpr int kLnFewRows = 5000;
 template <typename In, int L, int NC>
 __global__ __launch_bounds__(kBlockThreads)
 void layernorm_kernel(const uint16_t* x, const uint16_t* __restrict__ gamma,          // y may be x: no restrict
